@@ -109,16 +109,17 @@ hz_status hz_ctx_memory(const hz_ctx *ctx, uint64_t *used_bytes, uint64_t *budge
  *                          wave's lanes stay one pixel tile)
  *   "march.blocks_per_cu"  cap on resident 256-thread workgroups per CU,
  *                          0 = as many as fit (default 0)
- *   "splat.method"         0 or 1: gather (one workgroup per 8x8xBZ voxel
- *                          brick, fixed FP32 summation order; the default), 2: scatter
+ *   "splat.method"         0 or 1: gather (fixed FP32 summation order; the
+ *                          default), 2: scatter
  *                          (voxel tiles with 64-bit fixed-point accumulation in
  *                          LDS; slower, for a support of up to ~16 cells per
  *                          tile axis, HZ_E_UNSUPPORTED beyond); both are
  *                          bitwise repeatable
- *   "splat.brick_z"        gather brick depth BZ: 4 or 8 voxels, 0 = the one
- *                          that brings the brick closer to twice as deep as
- *                          wide (default 0)
- *   "splat.order"          1: the gather hands out its bricks heaviest first,
+ *   "splat.brick_z"        4 or 8: the column gather, in bricks of 8x8x4 or
+ *                          8x8x8 voxels; 0: the tile gather, or on a large
+ *                          fine grid with few particles the column gather
+ *                          (default 0)
+ *   "splat.order"          1: the column gather hands out its bricks heaviest first,
  *                          by each brick's candidate count in the context's
  *                          previous gather over the same bricks (up to 65,536
  *                          bricks); 0: in index order.  The field is the same

@@ -51,11 +51,21 @@ struct ScanGuard {
     uint32_t serial;
 };
 
+// Geometry of the tile gather, in units of 2h.
+struct TileGeom {
+    double c0[3];    // minus the grid's lower corner
+    double sp[3];    // voxel spacing
+    float scale;     // 1 / 2h (c0 and sp are scaled by exactly this float)
+    float u[3];      // voxel spacing
+    float half[3];   // half extents of a block of 4 x 4 x 2 voxel centres, grown by 1e-5
+};
+
 // Geometry and constants of one splat launch.
 struct SplatParams {
     float lo[3];          // grid box corner
     float sp[3];          // voxel spacing
     int32_t res[3];
+    int32_t tiles;         // tile gather (bricks of 8 x 8 x 4 voxels) instead of the column gather
     int32_t bz;            // gather brick depth: 4 or 8 voxels
     int32_t nbx, nby, nbz; // gather bricks (SPLAT_BX x SPLAT_BY x bz voxels) per axis
     float h;
@@ -63,6 +73,7 @@ struct SplatParams {
     float support2;       // (2h)^2
     float scale;          // k_gd / (pi h^3)
     CellGrid cg;
+    TileGeom tile;
 };
 
 // ---------------------------------------------------------------------------

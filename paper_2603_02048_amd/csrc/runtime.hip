@@ -24,7 +24,7 @@
 namespace haze {
 hipError_t launch_cell_list(const float *, const float *, const float *, const float *, int32_t, const CellGrid &,
                             uint32_t *, uint32_t *, int64_t, uint32_t *, uint32_t *, uint32_t *, float4 *, void *,
-                            bool, uint32_t *, bool, const ScanGuard &, uint32_t *, int32_t, bool, hipStream_t,
+                            bool, uint32_t *, bool, const ScanGuard &, uint32_t *, int32_t, bool, bool, hipStream_t,
                             const KTimer &);
 int32_t scan_tiles(int32_t ncells);
 size_t scan_scratch_bytes(int32_t ncells);
@@ -859,12 +859,33 @@ extern "C" hz_status hz_splat_index_field(hz_ctx *c, const hz_particles *P, cons
         sp.bz = c->splat_brick_z;
     else
         sp.bz = (double)sp.sp[2] <= 2.82842712 * 0.5 * ((double)sp.sp[0] + (double)sp.sp[1]) ? 8 : 4;
+    // The tile gather, unless a brick depth of the column gather is asked for,
+    // or a large fine grid holds few particles: there a wave of the tile
+    // gather has little to do per octant, and the column gather's larger
+    // bricks are faster.  Cell list and splat, tile / column, at 160^3 voxels:
+    // support of 10 voxels, 35 neighbours 161 / 155 us, 70 neighbours 207 / 212;
+    // support of 8 voxels, 35 neighbours 163 / 167; 256^3, support of 10 voxels,
+    // 27 neighbours 545 / 492.
+    const double cellv = (double)sp.sp[0] * sp.sp[1] * sp.sp[2], ball = 4.0 / 3.0 * M_PI * 8.0 * h * h * h;
+    const double nvox = (double)g->res[0] * g->res[1] * g->res[2];
+    const bool sparse = nvox >= (double)(1 << 21) && ball >= 4.0 / 3.0 * M_PI * 729.0 * cellv &&
+                        (double)P->n * ball < 50.0 * cellv * nvox;
+    sp.tiles = c->splat_brick_z == 0 && !sparse;
+    if (sp.tiles) sp.bz = 4;
     sp.nbz = (g->res[2] + sp.bz - 1) / sp.bz;
     sp.h = prm->h;
     sp.inv_h = (float)(1.0 / h);
     sp.support2 = (float)(4.0 * h * h);
     sp.scale = (float)((double)prm->k_gd / (M_PI * h * h * h));
     sp.cg = cg;
+    sp.tile.scale = (float)(0.5 / h);
+    for (int a = 0; a < 3; ++a) {
+        const double scale = (double)sp.tile.scale, spacing = (g->hi[a] - g->lo[a]) / g->res[a];
+        sp.tile.c0[a] = -g->lo[a] * scale;
+        sp.tile.sp[a] = spacing * scale;
+        sp.tile.u[a] = (float)(spacing * scale);
+        sp.tile.half[a] = (float)((a < 2 ? 1.5 : 0.5) * spacing * scale + 1e-5);
+    }
 
     HZ_HIP(hipSetDevice(c->device), "hipSetDevice");
     hipStream_t s = (hipStream_t)hip_stream;
@@ -889,7 +910,7 @@ extern "C" hz_status hz_splat_index_field(hz_ctx *c, const hz_particles *P, cons
     const int32_t nbricks = sp.nbx * sp.nby * sp.nbz;
     uint32_t *bwork = nullptr, *border = nullptr;
     bool ordered = false;
-    const bool record = !scatter && nbricks <= kMaxOrderedBricks;
+    const bool record = !scatter && !sp.tiles && nbricks <= kMaxOrderedBricks;
     if (record) {
         const bool same = c->brick_dims[0] == sp.nbx && c->brick_dims[1] == sp.nby && c->brick_dims[2] == sp.nbz &&
                           c->brick_dims[3] == sp.bz;
@@ -928,7 +949,7 @@ extern "C" hz_status hz_splat_index_field(hz_ctx *c, const hz_particles *P, cons
     hipError_t e = launch_cell_list(P->x, P->y, P->z, P->m, n, cg, (uint32_t *)c->cid.ptr, (uint32_t *)c->count.ptr,
                                     clear_words, (uint32_t *)c->start.ptr, (uint32_t *)c->lrank.ptr,
                                     (uint32_t *)c->slots.ptr, (float4 *)c->sorted.ptr, c->tiles.ptr, scan_reset,
-                                    &c->scan_base, scatter, guard, bwork, nbricks, ordered, s, t0);
+                                    &c->scan_base, scatter, guard, bwork, nbricks, ordered, sp.tiles && !scatter, s, t0);
     prof_commit(c, "cell_list", t0);
     if (e == hipSuccess) {
         c->count.clean = !scatter;

@@ -8,17 +8,21 @@
 // Pipeline (all integer work exact, so the result is bitwise repeatable):
 //   k_cell_count   particle -> cell id (cells of edge h over the grid box grown
 //                  by 2h), integer histogram with atomics; one more workgroup
-//                  buckets the gather's bricks by weight (order_bricks_count)
+//                  buckets the column gather's bricks by weight (order_bricks_count)
 //   k_scan_onepass exclusive prefix sum of the histogram in one launch
 //                  (tile sums published with tickets, lower tiles added);
 //                  k_scan_* in three passes for very large cell counts
 //   k_cell_scatter particle index -> its slot (cell start + arrival rank from
 //                  the histogram atomics: an arbitrary order inside the cell)
 //   k_cell_order   per particle, its rank by index among its cell's members
-//                  (stable order); (x, y, z, m) into cell-sorted float4 records;
-//                  one more workgroup lists the bricks heaviest first
-//                  (order_bricks_place)
-//   k_splat        one workgroup per 8x8x4 or 8x8x8 voxel brick (records the
+//                  (stable order); (x, y, z, m) into cell-sorted float4 records
+//                  (cbrt(m) for the tile gather); one more workgroup lists the
+//                  column gather's bricks heaviest first (order_bricks_place)
+//   k_splat_tiles  tile gather, the usual one: a wave per octant of 4x4x4
+//                  voxels compacts the particles in reach of its blocks of
+//                  4x4x2 in LDS and sums them in tiles of 16 particles x 32
+//                  voxels, in a fixed order
+//   k_splat        column gather: one workgroup per 8x8x4 or 8x8x8 voxel brick (records the
 //                  brick's candidate count for the next call's order), its cell-list
 //                  rows dealt to four waves: every lane owns a column of
 //                  voxels; each candidate particle is culled to the planes
@@ -388,7 +392,7 @@ __global__ __launch_bounds__(256) void k_cell_order(const uint32_t *__restrict__
                                                     const float *__restrict__ x, const float *__restrict__ y,
                                                     const float *__restrict__ z, const float *__restrict__ m,
                                                     float4 *__restrict__ sorted, const uint32_t *__restrict__ fail,
-                                                    BrickOrder O)
+                                                    int32_t mass_root, BrickOrder O)
 {
     // When ordering the gather's bricks, workgroup 0 places them (the second
     // phase) beside the ordering of the particles (one workgroup later).
@@ -405,7 +409,9 @@ __global__ __launch_bounds__(256) void k_cell_order(const uint32_t *__restrict__
     const uint32_t c = cid[i];
     if (c == 0xffffffffu) return;
     const uint32_t b = start[c], e = start[c + 1];
-    const float4 rec = make_float4(x[i], y[i], z[i], m[i]);
+    float4 rec = make_float4(x[i], y[i], z[i], m[i]);
+    // the tile gather takes the mass's cube root (rounded once, from double)
+    if (mass_root) rec.w = (float)cbrt((double)rec.w);
     // Eight slots per round with all eight loads in flight before any compare
     // (the loop is latency-bound); indices are clamped into the cell, which
     // holds at least particle i, and a clamped repeat is not counted.
@@ -686,6 +692,331 @@ __global__ __launch_bounds__(64 * SPLAT_WAVES) void k_splat(SplatParams P, const
             if (vz0 + v < P.res[2]) dn[((int64_t)vy * P.res[0] + vx) * P.res[2] + vz0 + v] = sum * sc;
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// tile gather: particles compacted per block of voxels, 16 x 32 pairs at a time
+// ---------------------------------------------------------------------------
+// Each wave owns an octant of 4 x 4 x 4 voxels (a workgroup of four waves a
+// brick of 8 x 8 x 4; the waves never meet) and sums its two blocks of
+// 4 x 4 x 2 together:
+//   1. It holds the octant's cell-list row ranges in its lanes (8 x 8 rows at a
+//      time) and reads the rows' particles 64 at a time, one per lane, packing
+//      short rows into one read, and one read ahead.
+//   2. Each particle is tested against the boxes of both blocks; those in
+//      reach go to a ring in LDS, one per block for the particles whose inner
+//      sphere (q < 1) reaches the block and one for the others.
+//   3. Sixteen ring entries form a tile of 16 particles x 32 voxels: a lane
+//      takes one particle (lane & 15) and the eight voxels (k, lane >> 4, g),
+//      whose distances share their differences per axis.  In units of 2h, with
+//      mu the cube root of the particle's mass (stored so by k_cell_order), a
+//      pair costs r = sqrt clamped to 1, w = mu - mu r, w^2 and an FMA:
+//      m t^3 = w^3 (see plane_terms for t and s); the pairs of an inner ring
+//      subtract m s^3 / 2 likewise, from 2r clamped to 1 and mu / cbrt(2).
+// What bounds it is VALU issue.  Measured on the card, in cycles of a SIMD per
+// wave64 instruction: FMA, add, multiply 2.5 as long as other waves can issue
+// beside it (about 4 straight after a square root), square root 8.3; 1,226 M
+// instructions at 256^3, 118 M of them square roots.  So the split aims at few
+// pair slots and few instructions per slot: blocks of 32 voxels fill 62% of
+// their slots with pairs in reach (the column gather's planes of 8 x 8 voxels
+// 45%), and a slot takes 6.6 instructions.  The squared distances on the
+// matrix cores (v_mfma_f32_16x16x4f32 of (-2v, 1) and (p, |p|^2)) were slower:
+// the FP32 MFMA does not run beside the VALU (8 cycles a slot, against 6 here).
+// Measured, column gather to tiles: 1,048,576 particles on 256^3 voxels 2,060
+// to 1,750 us; 262,144 on 128^3 320 to 245; 16,384 on 64^3 36 to 19; 3,000 on
+// 21x17x13 71 to 18 (here the column gather walks its rows one after another).
+// Every sum runs in a fixed order (ring order within a lane, then the sixteen
+// lanes), so the field is bitwise repeatable.
+constexpr int TILE_BX = 8, TILE_BY = 8, TILE_BZ = 4;   // a workgroup's voxels
+constexpr int TILE_RING = 80;                          // ring entries: 15 left over + 64 appended, in whole tiles
+
+// The lane's rank among the lanes of `mask`, from `base`.
+__device__ __forceinline__ uint32_t lane_rank(uint64_t mask, uint32_t base)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
+}
+
+// The value in a vector register.
+__device__ __forceinline__ float in_vgpr(float x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// The lanes below n (n <= 64).
+__device__ __forceinline__ uint64_t lanes_below(uint32_t n) { return n >= 64u ? ~0ull : (1ull << n) - 1ull; }
+
+// The voxels of one lane in a block's tiles: (k, y, g) with k = 0..3, y = lane
+// >> 4, g = 0, 1; coordinates from the octant's centre in units of 2h.
+struct TileVoxels {
+    float x[4], y, z[2];
+};
+
+// One tile: 16 ring entries against a block's 32 voxels; q is the lane's entry
+// (position, mass root), acc the sums of its eight voxels.
+template <bool INNER>
+__device__ __forceinline__ void tile_terms(const float4 &q, const TileVoxels &V, float acc[2][4])
+{
+    const float dy = V.y - q.y;
+    float dx2[4], r2[2][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float dx = V.x[k] - q.x;
+        dx2[k] = fmaf(dx, dx, dy * dy);
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const float dz = V.z[g] - q.z;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r2[g][k] = fmaf(dz, dz, dx2[k]);
+    }
+    const float mu = q.w, mi = 0.793700526f * mu;   // mu / cbrt(2)
+    float r[8], w[8], w2[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        r[i] = clamp01(__builtin_amdgcn_sqrtf(r2[i >> 2][i & 3]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = fmaf(-r[i], mu, mu);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w2[i] = w[i] * w[i];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i >> 2][i & 3] = fmaf(w2[i], w[i], acc[i >> 2][i & 3]);
+    if (INNER) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = fmaf(-clamp01(r[i] + r[i]), mi, mi);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w2[i] = -(w[i] * w[i]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i >> 2][i & 3] = fmaf(w2[i], w[i], acc[i >> 2][i & 3]);
+    }
+}
+
+// A ring's fill: `n` entries from `head` (a multiple of 16).
+struct Ring {
+    uint32_t head = 0u, n = 0u;
+};
+
+// The place of the lane's entry when the lanes of `mask` are appended.
+__device__ __forceinline__ uint32_t ring_place(const Ring &R, uint64_t mask)
+{
+    const uint32_t at = lane_rank(mask, R.head + R.n);
+    return min(at, at - (uint32_t)TILE_RING);   // wraps (at - TILE_RING is huge while at < TILE_RING)
+}
+
+// Takes the whole tiles of a ring; `q` is this lane's entry of the first tile
+// (entry lane & 15).
+template <bool INNER>
+__device__ __forceinline__ void ring_drain(const float4 *q, Ring &R, const TileVoxels &V, float acc[2][4])
+{
+    while (R.n >= 16u) {
+        tile_terms<INNER>(q[R.head], V, acc);
+        R.head += 16u;
+        if (R.head >= (uint32_t)TILE_RING) R.head = 0u;
+        R.n -= 16u;
+    }
+}
+
+// Orders a wave's own LDS writes before its other lanes' reads of them (DS
+// operations of one wave execute in order; this keeps the compiler to it).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// One step of summing 2 N values over the 16 lanes of a row, each lane keeping
+// half of them (the upper half where its bit N is set) and taking its
+// partner's share of that half (DPP: a lane that differs in bit N, and whose
+// sums so far come from other lanes).
+template <int N, int DPP>
+__device__ __forceinline__ void halve(float *v, int lane)
+{
+    const bool up = lane & N;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float mine = up ? v[i + N] : v[i], other = up ? v[i] : v[i + N];
+        v[i] = mine + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(other), DPP, 0xf, 0xf, true));
+    }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6)))
+void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const float4 *__restrict__ parts,
+                   int32_t nbricks, float *__restrict__ dn, const uint32_t *__restrict__ fail)
+{
+    // per wave: outer and inner ring of block 0, outer and inner ring of block 1
+    __shared__ float4 rings[4][4 * TILE_RING];
+    const int32_t brick = (int32_t)blockIdx.x;
+    if (brick >= nbricks) return;
+    const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, comp = lane >> 4;
+    const int32_t o0[3] = {brick % P.nbx * TILE_BX + 4 * (wave & 1), brick / P.nbx % P.nby * TILE_BY + 4 * (wave >> 1),
+                           brick / (P.nbx * P.nby) * TILE_BZ};
+    if (o0[0] >= P.res[0] || o0[1] >= P.res[1]) return;   // (waves never meet at a barrier)
+    // Positions below are from the octant's centre in units of 2h: x = p scale +
+    // c, with c the rounded -(centre) scale; what rounding took from c is taken
+    // off the voxels too.
+    const TileGeom &T = P.tile;
+    float c[3], e[3], half[3], blo[3], bhi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double cd = fma((double)(o0[a] + 2), -T.sp[a], T.c0[a]);
+        c[a] = (float)cd;
+        e[a] = (float)(cd - (double)c[a]);
+        half[a] = in_vgpr(T.half[a] + fabsf(e[a]));
+        // the octant's box of voxel centres
+        blo[a] = P.lo[a] + ((float)o0[a] + 0.5f) * P.sp[a];
+        bhi[a] = P.lo[a] + ((float)o0[a] + 3.5f) * P.sp[a];
+    }
+    const float R = 2.0f * P.h;
+    const bool second = o0[2] + 2 < P.res[2];   // the second block has voxels
+    TileVoxels vox[2];
+#pragma unroll
+    for (int zb = 0; zb < 2; ++zb) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) vox[zb].x[k] = in_vgpr(fmaf((float)k - 1.5f, T.u[0], -e[0]));
+        vox[zb].y = fmaf((float)comp - 1.5f, T.u[1], -e[1]);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) vox[zb].z[g] = in_vgpr(fmaf((float)(2 * zb + g) - 1.5f, T.u[2], -e[2]));
+    }
+    float acc[4][4] = {};
+
+    // cell rows that may hold a particle in reach (the slack absorbs rounding:
+    // cell numbers have a relative error of a few units in the last place)
+    const CellGrid &cg = P.cg;
+    const float ys = 1e-3f + 1e-6f * (float)cg.nc[1], zs = 1e-3f + 1e-6f * (float)cg.nc[2];
+    const int cz0 = max(0, (int)floorf((blo[2] - R - cg.clo[2]) * cg.inv_cell - zs));
+    const int cz1 = min(cg.nc[2] - 1, (int)floorf((bhi[2] + R - cg.clo[2]) * cg.inv_cell + zs));
+    const int cy0 = max(0, (int)floorf((blo[1] - R - cg.clo[1]) * cg.inv_cell - ys));
+    const int cy1 = min(cg.nc[1] - 1, (int)floorf((bhi[1] + R - cg.clo[1]) * cg.inv_cell + ys));
+    const bool bad = *fail != 0u;
+
+    // row ranges in the lanes: rows (py + (lane & 7), pz + (lane >> 3)) of a
+    // patch of 8 x 8; rows of it still to be read; what is left of the current one
+    // (no rows, and NaN voxels, when the cell-list scan failed)
+    uint32_t rs = 0u, re = 0u;
+    int py = cy0, pz = bad || cy0 > cy1 ? cz1 + 1 : cz0;   // the next patch
+    uint64_t todo = 0ull;
+    uint32_t cs = 0u, ce = 0u;
+    // the next particles of the rows, one per lane; returns how many lanes have one
+    const auto next = [&](float4 &q) -> uint32_t {
+        uint32_t at = 0u, filled = 0u;
+        while (filled < 64u) {
+            if (cs == ce) {
+                while (todo == 0ull && pz <= cz1) {
+                    const int cy = py + (lane & 7), cz = pz + (lane >> 3);
+                    py += 8;
+                    if (py > cy1) {
+                        py = cy0;
+                        pz += 8;
+                    }
+                    rs = re = 0u;
+                    if (cy <= cy1 && cz <= cz1) {
+                        const float zl = cg.clo[2] + (float)cz * cg.cell, yl = cg.clo[1] + (float)cy * cg.cell;
+                        const float gz = fmaxf(0.0f, fmaxf(zl - bhi[2], blo[2] - (zl + cg.cell)));
+                        const float gy = fmaxf(0.0f, fmaxf(yl - bhi[1], blo[1] - (yl + cg.cell)));
+                        // 1.0001 R^2 keeps the cut conservative under rounding
+                        const float rem = 1.0001f * P.support2 - gz * gz - gy * gy;
+                        const float dxm = __builtin_amdgcn_sqrtf(fmaxf(rem, 0.0f));
+                        const int kx0 = max(0, (int)floorf((blo[0] - dxm - cg.clo[0]) * cg.inv_cell));
+                        const int kx1 = min(cg.nc[0] - 1, (int)floorf((bhi[0] + dxm - cg.clo[0]) * cg.inv_cell));
+                        if (rem > 0.0f && kx0 <= kx1) {
+                            const int row = (cz * cg.nc[1] + cy) * cg.nc[0];
+                            rs = start[row + kx0];
+                            re = start[row + kx1 + 1];
+                        }
+                    }
+                    todo = __builtin_amdgcn_ballot_w64(rs < re);
+                }
+                if (todo == 0ull) break;
+                const int l = __builtin_ctzll(todo);
+                todo &= todo - 1ull;
+                cs = __builtin_amdgcn_readlane(rs, l);
+                ce = __builtin_amdgcn_readlane(re, l);
+            }
+            const uint32_t take = min(64u - filled, ce - cs);
+            if (__builtin_amdgcn_inverse_ballot_w64(~lanes_below(filled))) at = cs - filled + (uint32_t)lane;
+            cs += take;
+            filled += take;
+        }
+        q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (__builtin_amdgcn_inverse_ballot_w64(lanes_below(filled))) q = parts[at];
+        return filled;
+    };
+
+    float4 *const my = rings[wave];
+    const float4 *const mine = my + (lane & 15);
+    Ring out0, in0, out1, in1;
+    // radii grown by 0.1%: rounding never drops a pair in reach
+    constexpr float RO2 = 1.001f, RI2 = 0.25025f;
+    const auto append = [&](int base, Ring &out, Ring &in, float d2, uint64_t valid, const float4 &rec) {
+        const bool near = d2 < RI2;
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(d2 < RO2) & valid;
+        const uint64_t mi = __builtin_amdgcn_ballot_w64(near) & hit, mo = hit & ~mi;
+        const uint32_t at_o = ring_place(out, mo) + (uint32_t)base;
+        const uint32_t at_i = ring_place(in, mi) + (uint32_t)(base + TILE_RING);
+        if (__builtin_amdgcn_inverse_ballot_w64(hit)) {
+            const uint32_t at = near ? at_i : at_o;
+            my[at] = rec;
+        }
+        out.n += (uint32_t)__popcll(mo);
+        in.n += (uint32_t)__popcll(mi);
+    };
+    const auto drain = [&]() {
+        wave_lds_fence();
+        ring_drain<false>(mine, out0, vox[0], acc);
+        ring_drain<true>(mine + TILE_RING, in0, vox[0], acc);
+        ring_drain<false>(mine + 2 * TILE_RING, out1, vox[1], acc + 2);
+        ring_drain<true>(mine + 3 * TILE_RING, in1, vox[1], acc + 2);
+        wave_lds_fence();
+    };
+    float4 q, q_next;
+    uint32_t cnt = next(q);
+#pragma unroll 1
+    while (cnt) {
+        const uint32_t cnt_next = next(q_next);
+        const float x = fmaf(q.x, T.scale, c[0]), y = fmaf(q.y, T.scale, c[1]), z = fmaf(q.z, T.scale, c[2]);
+        const float ex = clamp01(fabsf(x) - half[0]), ey = clamp01(fabsf(y) - half[1]);
+        const float exy = fmaf(ex, ex, ey * ey);
+        const float4 rec = make_float4(x, y, z, q.w);
+        const uint64_t valid = lanes_below(cnt);
+        // the blocks' centres lie one voxel below and above the octant's
+        const float ez0 = clamp01(fabsf(z + T.u[2]) - half[2]), ez1 = clamp01(fabsf(z - T.u[2]) - half[2]);
+        append(0, out0, in0, fmaf(ez0, ez0, exy), valid, rec);
+        append(2 * TILE_RING, out1, in1, fmaf(ez1, ez1, exy), second ? valid : 0ull, rec);
+        drain();
+        q = q_next;
+        cnt = cnt_next;
+    }
+    // fill the last tiles up with entries out of reach and without mass
+    const auto pad = [&](int base, Ring &R) {
+        if (!R.n) return;
+        const uint64_t mask = lanes_below(16u - R.n);
+        const uint32_t at = ring_place(R, mask) + (uint32_t)base;
+        if (__builtin_amdgcn_inverse_ballot_w64(mask)) {
+            my[at] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        R.n = 16u;
+    };
+    pad(0, out0);
+    pad(TILE_RING, in0);
+    pad(2 * TILE_RING, out1);
+    pad(3 * TILE_RING, in1);
+    drain();
+
+    // Sum m W / sigma = 2 sum (m t^3 - m s^3 / 2), over the sixteen lanes of a
+    // row; lane j of row y ends with, and stores, voxel (j & 3, y, j >> 2).
+    float sum[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum[i] = acc[i >> 2][i & 3];
+    halve<8, 0x128>(sum, lane);   // row_ror:8, the lane ^ 8
+    halve<4, 0x141>(sum, lane);   // row_half_mirror, ^ 7
+    halve<2, 0x1b>(sum, lane);    // quad_perm:[3,2,1,0], ^ 3
+    halve<1, 0xb1>(sum, lane);    // quad_perm:[1,0,3,2], ^ 1
+    const int32_t vx = o0[0] + (lane & 3), vy = o0[1] + comp, vz = o0[2] + ((lane >> 2) & 3);
+    if (vx < P.res[0] && vy < P.res[1] && vz < P.res[2])
+        dn[((int64_t)vy * P.res[0] + vx) * P.res[2] + vz] = bad ? __builtin_nanf("") : sum[0] * (2.0f * P.scale);
 }
 
 // ---------------------------------------------------------------------------
@@ -1007,7 +1338,7 @@ hipError_t launch_cell_list(const float *x, const float *y, const float *z, cons
                             const CellGrid &cg, uint32_t *cid, uint32_t *count, int64_t count_clear_words,
                             uint32_t *start, uint32_t *lrank, uint32_t *slots, float4 *sorted, void *scan,
                             bool scan_reset, uint32_t *scan_base, bool want_mmax, const ScanGuard &guard,
-                            uint32_t *bwork, int32_t nbricks, bool order, hipStream_t s, const KTimer &t)
+                            uint32_t *bwork, int32_t nbricks, bool order, bool mass_root, hipStream_t s, const KTimer &t)
 {
     // The counts must start at zero; each scan leaves them so.
     // count[ncells+1] holds max |m| (scatter splat only), which the caller
@@ -1058,7 +1389,7 @@ hipError_t launch_cell_list(const float *x, const float *y, const float *z, cons
     hipLaunchKernelGGL(k_cell_scatter, dim3(blocks_for(n, 256)), dim3(256), 0, s, cid, lrank, n, start, slots,
                        fail);
     hipExtLaunchKernelGGL(k_cell_order, dim3(blocks_for(n, 256) + (O.order ? 1 : 0)), dim3(256), 0, s, nullptr,
-                          t.stop, 0, cid, start, slots, n, x, y, z, m, sorted, fail, O);
+                          t.stop, 0, cid, start, slots, n, x, y, z, m, sorted, fail, mass_root ? 1 : 0, O);
     return hipGetLastError();
 }
 
@@ -1071,7 +1402,10 @@ hipError_t launch_splat(const SplatParams &P, const uint32_t *start, const float
 {
     const int32_t nbricks = P.nbx * P.nby * P.nbz;
     const dim3 g((unsigned)nbricks), b(64 * SPLAT_WAVES);
-    if (P.bz == 8)
+    if (P.tiles)
+        hipExtLaunchKernelGGL(k_splat_tiles, g, dim3(256), 0, s, t.start, t.stop, 0, P, start, sorted, nbricks, dn,
+                              fail);
+    else if (P.bz == 8)
         hipExtLaunchKernelGGL(k_splat<8>, g, b, 0, s, t.start, t.stop, 0, P, start, sorted, nbricks, dn,
                               fail, bwork, border);
     else

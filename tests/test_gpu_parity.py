@@ -92,6 +92,28 @@ def test_splat_parity_small(ctx, haze, seed, res, h, method):
         _default(ctx)
 
 
+# the default gather at the edges of its octants of 4 x 4 x 4 voxels and blocks
+# of 4 x 4 x 2 (one voxel past them, one short of them, two voxels in all), at
+# coarse and fine voxels against h, at more rows of cells and more particles
+# per cell than a wave reads at once, and at mixed signs of the masses
+@pytest.mark.parametrize("res,h,n,signs", [((2, 2, 2), 0.2, 400, 1), ((5, 4, 3), 0.05, 3000, 1),
+                                           ((4, 9, 7), 0.04, 3000, 1), ((21, 17, 13), 0.03, 6000, 1),
+                                           ((8, 8, 6), 0.006, 6000, 1), ((33, 30, 41), 0.02, 20000, 1),
+                                           ((12, 10, 9), 0.3, 20000, 1), ((13, 24, 6), 0.03, 6000, -1)])
+def test_splat_tiles_parity(ctx, haze, res, h, n, signs):
+    wl = W.make_small(seed=21, res=res, h=h, n=n)
+    if signs < 0:
+        wl.particles.m[::3] *= -0.5
+    field, md = _splat_both(ctx, haze, wl)
+    dn, gx, gy, gz = _field_np(ctx, field)
+    assert_field_match(dn, (gx, gy, gz), md.arrays[0], md.arrays[1:], wl.grid.spacing, f"splat tiles res={res} h={h}")
+    again = ctx.splat_index_field(haze.upload_particles(wl.particles), wl.grid, wl.k_gd, wl.h)
+    for x, y in zip((dn, gx, gy, gz), _field_np(ctx, again)):
+        assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+    field.release()
+    again.release()
+
+
 @pytest.mark.parametrize("method", ["gather", "gather8", "scatter"])
 def test_splat_is_bitwise_repeatable(ctx, haze, method):
     _use(ctx, method)
