@@ -1347,7 +1347,7 @@ static hz_status prepare_trace(hz_ctx *c, const hz_field *fc, const hz_view *vie
 // Persistent march grid: what fits on the chip at once.
 static int march_grid_blocks(const hz_ctx *c, const TraceLaunch &L, int dt)
 {
-    const int64_t want_blocks = (L.nslots + 255) / 256;
+    const int64_t want_blocks = march_useful_blocks(L.nslots);
     const int fit = L.mesh.ntris > 0 ? c->march_bpc_scene[2][dt]
                     : L.ninner > 0   ? c->march_bpc_scene[1][dt]
                     : L.nquads > 0   ? c->march_bpc_scene[0][dt]

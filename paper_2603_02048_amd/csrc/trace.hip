@@ -668,14 +668,18 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
     const int lane = threadIdx.x & 63;
 
     // Work distribution over the length-sorted hits.  Wave w first takes
-    // hits [64 w, 64 w + 64) with no atomic; later batches of 64 come from one
+    // hits [sb w, sb w + sb) with no atomic; later batches of 64 come from one
     // counter past the static range, fetched one batch ahead (the atomic's
     // latency hides behind the march).  Each wave keeps its reserve
-    // [next, end) of hit indices.
+    // [next, end) of hit indices.  With no more batches than workgroups the
+    // waves are numbered across the workgroups, else along them (neighbouring
+    // tiles then share a compute unit's L1).
     const uint32_t blk = blockIdx.x, nblk = gridDim.x;
-    const uint32_t nwaves = nblk * (blockDim.x >> 6);
-    const uint32_t wave_id = __builtin_amdgcn_readfirstlane(blk * (blockDim.x >> 6) + (threadIdx.x >> 6));
-    const uint32_t sb = 64u;
+    const uint32_t wpb = blockDim.x >> 6, nwaves = nblk * wpb;
+    const uint32_t sb = march_batch(nh);
+    const bool across = (uint64_t)nblk * sb >= nh;
+    const uint32_t wib = threadIdx.x >> 6;
+    const uint32_t wave_id = __builtin_amdgcn_readfirstlane(across ? blk + nblk * wib : blk * wpb + wib);
     const uint32_t dyn0 = nwaves * sb;
     uint32_t next = min(wave_id * sb, nh);
     uint32_t end = min(next + sb, nh);

@@ -388,6 +388,22 @@ def test_trace_edge_cases(ctx, haze):
     field.release()
 
 
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 64, 65, 1024, 4095, 4097, 16389, 40000])
+def test_few_rays_equal_the_full_launch(ctx, haze, n):
+    """The march deals few rays in smaller batches: whatever the batch, a ray's
+    outputs are the bits of the launch of all rays."""
+    wl = W.make_small(seed=14, width=241, height=167, nviews=1)
+    print(f"case {n} of {wl.nrays} rays", flush=True)
+    field = ctx.splat_index_field(haze.upload_particles(wl.particles), wl.grid, wl.k_gd, wl.h)
+    full = ctx.trace_views(field, wl.views, wl.step_adaptive)
+    ids = torch.from_numpy(W.draw_subset(wl.nrays, n, 3)).cuda()
+    sub = ctx.trace_views(field, wl.views, wl.step_adaptive, ray_ids=ids)
+    for k, v in sub.items():
+        a, b = v.cpu().numpy(), full[k][ids].cpu().numpy()
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), k
+    field.release()
+
+
 def test_tune_keys_checked(ctx, haze):
     for key, bad in (("march.refill_min", 0), ("march.refill_min", 65), ("march.blocks_per_cu", -1),
                      ("march.blocks_per_cu", 65), ("splat.method", 3), ("splat.brick_z", 5), ("splat.brick_z", 16),
