@@ -1243,12 +1243,10 @@ __device__ __forceinline__ float central(float fm, float c, float fp, int32_t id
 // marches spans a few voxels in z and in one horizontal axis, and with z
 // fastest its rows share cache lines whichever horizontal direction the view
 // looks along (with x fastest, views along x gathered from twice the lines).
-// delta_n is read with strides (dsx, dsy, dsz): z-fast from the splat,
-// [z][y][x] from hz_index_field_from_grid.
+// delta_n is read z-fast, as the splat writes it.
 template <int DT>
-__global__ __launch_bounds__(256) void k_grad_pack(const float *__restrict__ dn, int32_t dsx, int32_t dsy,
-                                                   int32_t dsz, int32_t rx, int32_t ry, int32_t rz, float ix,
-                                                   float iy, float iz, float scale, int32_t gz, int32_t gx,
+__global__ __launch_bounds__(256) void k_grad_pack(const float *__restrict__ dn, int32_t rx, int32_t ry, int32_t rz,
+                                                   float ix, float iy, float iz, float scale, int32_t gz, int32_t gx,
                                                    int32_t nblocks, int32_t per_xcd, void *__restrict__ out)
 {
     // blocks (z, x, y) in that order, each XCD (workgroups are dealt
@@ -1262,62 +1260,159 @@ __global__ __launch_bounds__(256) void k_grad_pack(const float *__restrict__ dn,
     const int32_t j0 = by * GP_Y;
     if (k >= rz || i >= rx) return;
     // voxel counts are below 2^31 (checked on the host): 32-bit index math
-    int32_t u = i * dsx + j0 * dsy + k * dsz;    // delta_n
-    int32_t v = (j0 * rx + i) * rz + k;          // packed voxel
+    int32_t v = (j0 * rx + i) * rz + k;          // voxel, in delta_n and packed
     const int32_t vy = rx * rz;
     // x and z neighbours (and the y ones, from the walk) stay inside the
     // grid: a face uses the one-sided difference
-    const int32_t xm = i > 0 ? -dsx : 0, xp = i < rx - 1 ? dsx : 0;
-    const int32_t zm = k > 0 ? -dsz : 0, zp = k < rz - 1 ? dsz : 0;
-    float ym = j0 > 0 ? dn[u - dsy] : 0.0f;
-    float c = dn[u];
+    const int32_t xm = i > 0 ? -rz : 0, xp = i < rx - 1 ? rz : 0;
+    const int32_t zm = k > 0 ? -1 : 0, zp = k < rz - 1 ? 1 : 0;
+    float ym = j0 > 0 ? dn[v - vy] : 0.0f;
+    float c = dn[v];
     const int32_t j1 = min(j0 + GP_Y, ry);
     for (int32_t j = j0; j < j1; ++j) {
-        const float yp = j + 1 < ry ? dn[u + dsy] : 0.0f;
-        const float gx = central(dn[u + xm], c, dn[u + xp], i, rx, ix);
+        const float yp = j + 1 < ry ? dn[v + vy] : 0.0f;
+        const float gx = central(dn[v + xm], c, dn[v + xp], i, rx, ix);
         const float gy = central(ym, c, yp, j, ry, iy);
-        const float gz = central(dn[u + zm], c, dn[u + zp], k, rz, iz);
+        const float gz = central(dn[v + zm], c, dn[v + zp], k, rz, iz);
         store_voxel<DT>(out, v, c, gx, gy, gz, scale);
         ym = c;
         c = yp;
-        u += dsy;
         v += vy;
     }
 }
 
-// Packed (z-fast) field -> [z][y][x] arrays: one thread per output voxel v.
+// The same from a [z][y][x] delta_n (hz_index_field_from_grid): reads want x,
+// the packed stores z, as the fastest lane index.  A workgroup walks `planes`
+// planes of 16 x 16 (x, z) voxels along y; each plane with its x and z
+// neighbours is read along x one plane ahead, put into LDS (three planes in
+// turn: one barrier per plane) and used along z, so a load covers 64 contiguous
+// bytes and a store 256 (F32) or 128.  Bound by memory: 256^3 voxels to BF16
+// take 41 us (201 MB: 40 us at the rate of a copy), to F32 90 us; read along z,
+// 4 useful bytes per lane and line, they took 192 and 224.  193x150x111 to
+// BF16: 39 to 16 us.
+constexpr int GPX_T = 16;
+
+template <int DT>
+__global__ __launch_bounds__(GPX_T * GPX_T) void k_grad_pack_xyz(const float *__restrict__ dn, int32_t rx, int32_t ry,
+                                                                 int32_t rz, float ix, float iy, float iz,
+                                                                 float scale, int32_t planes, void *__restrict__ out)
+{
+    constexpr int HALO = GPX_T + 2, CELLS = HALO * HALO, PER = (CELLS + GPX_T * GPX_T - 1) / (GPX_T * GPX_T);
+    __shared__ float plane[3][HALO][HALO + 1];   // [z][x], with one neighbour on either side
+    const int32_t k0 = (int32_t)blockIdx.x * GPX_T, i0 = (int32_t)blockIdx.y * GPX_T, j0 = (int32_t)blockIdx.z * planes;
+    const int32_t j1 = min(j0 + planes, ry);
+    // this thread's share of a plane: read along x, kept in registers until
+    // the plane's turn (neighbours beyond the grid repeat the face, whose
+    // one-sided difference does not use them)
+    const float *src[PER];
+    float ahead[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int t = min((int)threadIdx.x + u * GPX_T * GPX_T, CELLS - 1);
+        const int z = t / HALO, x = t - z * HALO;
+        const int32_t k = min(max(k0 + z - 1, 0), rz - 1), i = min(max(i0 + x - 1, 0), rx - 1);
+        src[u] = dn + ((int64_t)k * ry + j0) * rx + i;
+    }
+    const auto read = [&]() {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            ahead[u] = *src[u];
+            src[u] += rx;
+        }
+    };
+    const auto put = [&](int b) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int t = min((int)threadIdx.x + u * GPX_T * GPX_T, CELLS - 1);
+            plane[b][t / HALO][t % HALO] = ahead[u];
+        }
+    };
+    // this thread's voxels: z fastest
+    const int z = (int)threadIdx.x & (GPX_T - 1), x = (int)threadIdx.x / GPX_T;
+    const int32_t k = k0 + z, i = i0 + x;
+    const bool mine = k < rz && i < rx;
+    float ym = mine && j0 > 0 ? dn[((int64_t)k * ry + j0 - 1) * rx + i] : 0.0f;
+    read();
+    put(0);
+    if (j0 + 1 < ry) read();
+    __syncthreads();
+    float c = plane[0][z + 1][x + 1];
+    int b = 0;
+    for (int32_t j = j0; j < j1; ++j) {
+        const int nb = b == 2 ? 0 : b + 1;
+        if (j + 1 < ry) {
+            put(nb);
+            if (j + 2 < ry && j + 1 < j1) read();
+        }
+        __syncthreads();
+        const float yp = j + 1 < ry ? plane[nb][z + 1][x + 1] : 0.0f;
+        if (mine) {
+            const float gx = central(plane[b][z + 1][x], c, plane[b][z + 1][x + 2], i, rx, ix);
+            const float gy = central(ym, c, yp, j, ry, iy);
+            const float gz = central(plane[b][z][x + 1], c, plane[b][z + 2][x + 1], k, rz, iz);
+            store_voxel<DT>(out, (j * rx + i) * rz + k, c, gx, gy, gz, scale);
+        }
+        ym = c;
+        c = yp;
+        b = nb;
+    }
+}
+
+// Packed (z-fast) field -> [z][y][x] arrays.  A workgroup takes 32 (x) x 16 (z)
+// voxels of one y, read along z and written along x through LDS: 256 (F32) or
+// 128 contiguous bytes a read, 128 a write.  One thread per output voxel,
+// reading across z-columns, took 192 us for a 256^3 F32 field; this 106 us
+// (537 MB: 106 us at the rate of a copy); 193x150x111 BF16 46 to 22 us.
+constexpr int UP_X = 32, UP_Z = 16;
+
 template <int DT>
 __global__ __launch_bounds__(256) void k_field_unpack(const void *__restrict__ in, int32_t rx, int32_t ry,
                                                       int32_t rz, float inv_scale, float *__restrict__ dn,
                                                       float *__restrict__ gx, float *__restrict__ gy,
                                                       float *__restrict__ gz)
 {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nxy = (int64_t)rx * ry;
-    if (v >= nxy * rz) return;
-    const int64_t k = v / nxy, r = v - k * nxy;
-    const int64_t w = r * rz + k;   // r = j rx + i
-    float4 f;
-    if (DT == DT_F32) {
-        f = reinterpret_cast<const float4 *>(in)[w];
-    } else {
-        const ushort4 h = reinterpret_cast<const ushort4 *>(in)[w];
-        if (DT == DT_F16) {
-            f = make_float4(__half2float(__ushort_as_half(h.x)), __half2float(__ushort_as_half(h.y)),
-                            __half2float(__ushort_as_half(h.z)), __half2float(__ushort_as_half(h.w)));
+    __shared__ float tile[4][UP_Z][UP_X + 1];
+    const int32_t k0 = (int32_t)blockIdx.x * UP_Z, i0 = (int32_t)blockIdx.y * UP_X, j = (int32_t)blockIdx.z;
+#pragma unroll
+    for (int t = 0; t < UP_X * UP_Z; t += 256) {
+        const int z = (t + (int)threadIdx.x) % UP_Z, x = (t + (int)threadIdx.x) / UP_Z;
+        const int32_t k = k0 + z, i = i0 + x;
+        if (k >= rz || i >= rx) continue;
+        const int64_t w = ((int64_t)j * rx + i) * rz + k;
+        float4 f;
+        if (DT == DT_F32) {
+            f = reinterpret_cast<const float4 *>(in)[w];
         } else {
-            f = make_float4(__uint_as_float((uint32_t)h.x << 16), __uint_as_float((uint32_t)h.y << 16),
-                            __uint_as_float((uint32_t)h.z << 16), __uint_as_float((uint32_t)h.w << 16));
+            const ushort4 h = reinterpret_cast<const ushort4 *>(in)[w];
+            if (DT == DT_F16) {
+                f = make_float4(__half2float(__ushort_as_half(h.x)), __half2float(__ushort_as_half(h.y)),
+                                __half2float(__ushort_as_half(h.z)), __half2float(__ushort_as_half(h.w)));
+            } else {
+                f = make_float4(__uint_as_float((uint32_t)h.x << 16), __uint_as_float((uint32_t)h.y << 16),
+                                __uint_as_float((uint32_t)h.z << 16), __uint_as_float((uint32_t)h.w << 16));
+            }
+            f.x *= inv_scale;
+            f.y *= inv_scale;
+            f.z *= inv_scale;
+            f.w *= inv_scale;
         }
-        f.x *= inv_scale;
-        f.y *= inv_scale;
-        f.z *= inv_scale;
-        f.w *= inv_scale;
+        tile[0][z][x] = f.x;
+        tile[1][z][x] = f.y;
+        tile[2][z][x] = f.z;
+        tile[3][z][x] = f.w;
     }
-    if (dn) dn[v] = f.x;
-    if (gx) gx[v] = f.y;
-    if (gy) gy[v] = f.z;
-    if (gz) gz[v] = f.w;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < UP_X * UP_Z; t += 256) {
+        const int x = (t + (int)threadIdx.x) % UP_X, z = (t + (int)threadIdx.x) / UP_X;
+        const int32_t k = k0 + z, i = i0 + x;
+        if (k >= rz || i >= rx) continue;
+        const int64_t v = ((int64_t)k * ry + j) * rx + i;
+        if (dn) dn[v] = tile[0][z][x];
+        if (gx) gx[v] = tile[1][z][x];
+        if (gy) gy[v] = tile[2][z][x];
+        if (gz) gz[v] = tile[3][z][x];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1414,32 +1509,48 @@ hipError_t launch_splat(const SplatParams &P, const uint32_t *start, const float
     return hipGetLastError();
 }
 
+template <int DT>
+static void launch_grad_pack_t(const float *dn, bool dn_zfast, const int32_t r[3], const float inv[3], float scale,
+                               void *out, hipStream_t s, const KTimer &t)
+{
+    if (dn_zfast) {
+        const int32_t gz = (r[2] + 63) / 64, gx = (r[0] + 3) / 4, gy = (r[1] + GP_Y - 1) / GP_Y;
+        const int32_t nblocks = gz * gx * gy, per_xcd = (nblocks + 7) / 8;
+        hipExtLaunchKernelGGL(k_grad_pack<DT>, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, s, t.start, t.stop, 0, dn,
+                              r[0], r[1], r[2], inv[0], inv[1], inv[2], scale, gz, gx, nblocks, per_xcd, out);
+    } else {
+        // Planes per workgroup: 8, as long as that leaves 1,024 workgroups, then
+        // 4 or 2.  With 8, 4 and 2 planes: 256^3 to F32 90, 98, 109 us; 64^3,
+        // where 8 planes leave 128 workgroups, 6.2, 5.0, 4.7.
+        const unsigned gz = (unsigned)((r[2] + GPX_T - 1) / GPX_T), gx = (unsigned)((r[0] + GPX_T - 1) / GPX_T);
+        int32_t planes = 8;
+        while (planes > 2 && (int64_t)gz * gx * ((r[1] + planes - 1) / planes) < 1024) planes >>= 1;
+        // (each axis has at most 65,535 voxels, so the grid's y and z fit)
+        hipExtLaunchKernelGGL(k_grad_pack_xyz<DT>, dim3(gz, gx, (unsigned)((r[1] + planes - 1) / planes)),
+                              dim3(GPX_T * GPX_T), 0, s, t.start, t.stop, 0, dn, r[0], r[1], r[2], inv[0], inv[1],
+                              inv[2], scale, planes, out);
+    }
+}
+
 // dn_zfast: delta_n as the splat writes it (z fastest: (j rx + i) rz + k);
 // otherwise [z][y][x].
 hipError_t launch_grad_pack(int dtype, const float *dn, bool dn_zfast, const int32_t res[3], const float inv_sp[3],
                             float scale, void *out, hipStream_t s, const KTimer &t)
 {
-    const int32_t gz = (res[2] + 63) / 64, gx = (res[0] + 3) / 4, gy = (res[1] + GP_Y - 1) / GP_Y;
-    const int32_t nblocks = gz * gx * gy, per_xcd = (nblocks + 7) / 8;
-    const dim3 g((unsigned)(per_xcd * 8)), b(256);
-    const int32_t dsx = dn_zfast ? res[2] : 1, dsy = dn_zfast ? res[0] * res[2] : res[0],
-                  dsz = dn_zfast ? 1 : res[0] * res[1];
     if (dtype == DT_F32)
-        hipExtLaunchKernelGGL(k_grad_pack<DT_F32>, g, b, 0, s, t.start, t.stop, 0, dn, dsx, dsy, dsz, res[0], res[1],
-                              res[2], inv_sp[0], inv_sp[1], inv_sp[2], scale, gz, gx, nblocks, per_xcd, out);
+        launch_grad_pack_t<DT_F32>(dn, dn_zfast, res, inv_sp, scale, out, s, t);
     else if (dtype == DT_F16)
-        hipExtLaunchKernelGGL(k_grad_pack<DT_F16>, g, b, 0, s, t.start, t.stop, 0, dn, dsx, dsy, dsz, res[0], res[1],
-                              res[2], inv_sp[0], inv_sp[1], inv_sp[2], scale, gz, gx, nblocks, per_xcd, out);
+        launch_grad_pack_t<DT_F16>(dn, dn_zfast, res, inv_sp, scale, out, s, t);
     else
-        hipExtLaunchKernelGGL(k_grad_pack<DT_BF16>, g, b, 0, s, t.start, t.stop, 0, dn, dsx, dsy, dsz, res[0],
-                              res[1], res[2], inv_sp[0], inv_sp[1], inv_sp[2], scale, gz, gx, nblocks, per_xcd, out);
+        launch_grad_pack_t<DT_BF16>(dn, dn_zfast, res, inv_sp, scale, out, s, t);
     return hipGetLastError();
 }
 
 hipError_t launch_field_unpack(int dtype, const void *in, const int32_t res[3], float inv_scale, float *dn, float *gx,
                                float *gy, float *gz, hipStream_t s)
 {
-    const dim3 g(blocks_for((int64_t)res[0] * res[1] * res[2], 256)), b(256);
+    const dim3 g((unsigned)((res[2] + UP_Z - 1) / UP_Z), (unsigned)((res[0] + UP_X - 1) / UP_X), (unsigned)res[1]);
+    const dim3 b(256);
     if (dtype == DT_F32)
         hipLaunchKernelGGL(k_field_unpack<DT_F32>, g, b, 0, s, in, res[0], res[1], res[2], inv_scale, dn, gx, gy, gz);
     else if (dtype == DT_F16)

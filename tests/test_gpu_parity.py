@@ -388,6 +388,30 @@ def test_trace_edge_cases(ctx, haze):
     field.release()
 
 
+@pytest.mark.parametrize("res", [(2, 2, 2), (3, 17, 2), (16, 16, 16), (17, 9, 33), (15, 40, 18), (33, 7, 47),
+                                 (70, 65, 64)])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_grid_import_and_read_back(ctx, haze, res, dtype):
+    """hz_index_field_from_grid and hz_field_read at the edges of their 16 x 16
+    and 32 x 16 tiles and walks: delta_n comes back as stored, the gradient
+    with at most the rounding of a float32 difference and of the storage."""
+    rng = np.random.default_rng(5)
+    grid = W.make_grid((0.1, 0.2, 0.3), (1.0, 0.9, 1.4), res)
+    dn = (2e-4 * (1.0 + 0.2 * rng.standard_normal(res[::-1]))).astype(np.float32)
+    scale = 1.0 if dtype == "f32" else 1e4
+    field = ctx.index_field_from_grid(torch.from_numpy(dn).cuda(), grid, dtype=dtype, store_scale=scale)
+    got = _field_np(ctx, field)
+    half = {"f32": 0.0, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype]   # relative rounding of a stored value
+    tiny = 2.0 ** -25 / scale                                          # half the least F16 step
+    assert np.all(np.abs(got[0] - dn) <= half * np.abs(dn) + (tiny if dtype == "f16" else 0.0))
+    for g, axis, d in zip(got[1:], (2, 1, 0), grid.spacing):
+        ref = np.gradient(dn.astype(np.float64), axis=axis) / d
+        # the difference and the product with 1 / spacing each round once
+        bound = 3 * 2.0 ** -24 * np.abs(dn).max() / d + (half + 2.0 ** -22) * np.abs(ref)
+        assert np.all(np.abs(g - ref) <= bound + (tiny if dtype == "f16" else 0.0)), axis
+    field.release()
+
+
 @pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 64, 65, 1024, 4095, 4097, 16389, 40000])
 def test_few_rays_equal_the_full_launch(ctx, haze, n):
     """The march deals few rays in smaller batches: whatever the batch, a ray's
