@@ -178,6 +178,7 @@ struct TraceLaunch {
     int32_t subset;        // 1: slots are positions in ray_ids; 0: 8x8 tile order over jobs
     int64_t nslots;
     const int64_t *ray_ids;
+    const void *field;     // the field of every job, or null: several, or one past one_field()
     TraceOutFlat flat;
     uint32_t *hits;        // slots of the rays that enter the volume, sorted by length bin
     uint8_t *slot_bin;     // per slot: length bin of an entering ray, 255 otherwise
@@ -193,6 +194,16 @@ struct TraceLaunch {
     const SceneQuad *quads;  // device copy of the nquads boards
     MeshLaunch mesh;       // triangle-mesh scene (mesh.ntris > 0), exclusive of boards
 };
+
+// The march addresses the one field of a launch with 32-bit offsets from bases
+// lowered by kFieldBias (see FieldRows in trace.hip).  The limits are those of
+// the arithmetic: 24-bit factors (columns; a column's bytes are below 2^20,
+// since an axis holds at most 65535 voxels), offset and bias together below 2^32.
+constexpr uint32_t kFieldBias = 0x4b000000u;   // the bits of 2^23 as a float
+inline bool one_field(const int32_t res[3], uint64_t bytes)
+{
+    return (int64_t)res[0] * res[1] < (1 << 24) && bytes < 0x100000000ull - kFieldBias;
+}
 
 // Ray generation sorts the entering rays by their straight chord through the
 // volume (a proxy for their step count), longest first, in kRayBins bins: the

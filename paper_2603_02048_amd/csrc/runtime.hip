@@ -1324,6 +1324,7 @@ static hz_status prepare_trace(hz_ctx *c, const hz_field *fc, const hz_view *vie
     L.subset = subset ? 1 : 0;
     L.nslots = subset ? nrays : slot;
     L.ray_ids = ray_ids;
+    L.field = one_field(f->grid.res, f->bytes) ? f->data : nullptr;
     L.flat = TraceOutFlat{out->disp, out->exit_pos, out->exit_dir, out->steps, out->status, surface, tri_tests};
     if (!subset)
         for (int i = 0; i < nviews; ++i) {
@@ -1557,6 +1558,7 @@ const hz_grid &field_grid(const hz_field *f) { return f->grid; }
 hz_dtype field_dtype(const hz_field *f) { return f->dtype; }
 float field_scale(const hz_field *f) { return f->store_scale; }
 const void *field_data(const hz_field *f) { return f->data; }
+uint64_t field_bytes(const hz_field *f) { return f->bytes; }
 hz_ctx *field_ctx(const hz_field *f) { return f->ctx; }
 hz_status ctx_mark(hz_ctx *c, hipStream_t s, CallMark *out) { return mark_issue(c, s, out); }
 hz_status ctx_mark_sync(hz_ctx *c, const CallMark &t) { return mark_sync(c, t); }

@@ -24,6 +24,7 @@ const hz_grid &field_grid(const hz_field *f);
 hz_dtype field_dtype(const hz_field *f);
 float field_scale(const hz_field *f);
 const void *field_data(const hz_field *f);
+uint64_t field_bytes(const hz_field *f);
 hz_ctx *field_ctx(const hz_field *f);
 hz_status field_ready(hz_field *f, hipStream_t s);       // order a read on s after the field's producer
 void field_use(hz_field *f, const CallMark &t);            // a read by the call with mark t

@@ -259,6 +259,9 @@ static hz_status launch_batch(Server *S, Slot &sl, std::vector<Request *> &batch
     L.subset = 0;
     L.nslots = slot;
     L.ray_ids = nullptr;
+    bool same = true;
+    for (const Request *r : batch) same = same && r->field == head->field;
+    L.field = same && one_field(field_grid(head->field).res, field_bytes(head->field)) ? field_data(head->field) : nullptr;
     L.hits = (uint32_t *)sl.hits;
     L.counters = (uint32_t *)sl.counters + (size_t)sl.counter_set * kCounterSetWords;
     L.counters_next = (uint32_t *)sl.counters + (size_t)(1 - sl.counter_set) * kCounterSetWords;

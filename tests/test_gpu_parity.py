@@ -6,6 +6,8 @@ partial 8x8 tiles), stress fields (K_GD x 200) where bending is large enough
 for the tolerances to bite, adaptive and fixed steps, analytic grids, and
 edge cases.  Every launch goes through libhaze.so.
 """
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -426,6 +428,55 @@ def test_few_rays_equal_the_full_launch(ctx, haze, n):
         a, b = v.cpu().numpy(), full[k][ids].cpu().numpy()
         assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), k
     field.release()
+
+
+@pytest.mark.parametrize("dtype,res", [
+    ("f32", (2, 2, 2)), ("f16", (2, 2, 2)), ("bf16", (2, 2, 2)), ("f32", (5, 2, 131)), ("f16", (3, 70, 33)),
+    ("bf16", (131, 2, 17)), ("f32", (67, 40, 51)), ("f16", (40, 67, 50)), ("bf16", (51, 43, 67)),
+    ("f16", (2, 2, 65535)), ("f16", (65535, 3, 2)), ("bf16", (4096, 4095, 2)), ("bf16", (4096, 4096, 2)),
+    ("f32", (574, 574, 574)), ("f32", (575, 575, 575))])
+def test_one_field_march_equals_a_mixed_batch(haze, dtype, res):
+    """A launch whose rays read one field takes 32-bit offsets from the field's
+    rows (up to 2^24 columns and about 2.8 GiB), a batch over two fields the
+    general addresses: the bits of every output are the same."""
+    print(f"case {dtype} {res}", flush=True)
+    ctx = haze.Context(0)
+    try:
+        grid = W.make_grid((0.0, 0.0, 0.0), (0.9, 0.8, 1.1), res)
+        axes = [torch.linspace(0.0, 1.0, r, device="cuda") for r in res]
+        fields = []
+        for k in range(2):
+            wave = [torch.sin((3.0 + k + a) * axes[a]) for a in range(3)]
+            dn = 3e-3 * (wave[2][:, None, None] * wave[1][None, :, None] + wave[0][None, None, :])
+            fields.append(ctx.index_field_from_grid(dn.contiguous(), grid, dtype=dtype,
+                                                    store_scale=1.0 if dtype == "f32" else 64.0))
+            del dn
+        views = [W.ring_view(grid.lo, grid.hi, 0.7 + 2.0 * k, 1.3, 61 + k, 37, backdrop_beyond=0.6) for k in range(2)]
+        step = W.make_steps(W.make_grid(grid.lo, grid.hi, (48, 48, 48)))[0]
+        ctx.profile_enable(True)
+        ctx.server_start(slots=1, max_batch_rays=1 << 16)
+        tickets = [(ctx.submit(fields[i & 1], views, step), i & 1) for i in range(12)]
+        _wait_all(ctx, [t for t, _ in tickets])
+        assert ctx.profile_read("serve_batch")[1] < len(tickets)   # at least one batch held both fields
+        solo = [to_np(ctx.trace_views(f, views, step)) for f in fields]
+        assert all((s["steps"] > 1).any() for s in solo)
+        for t, k in tickets:
+            got = to_np(ctx.request_outputs(t))
+            torch.cuda.synchronize()
+            for name, ref in solo[k].items():
+                assert np.array_equal(got[name].view(np.uint8), ref.view(np.uint8)), (t, name)
+            ctx.request_release(t)
+        ctx.server_stop()
+    finally:
+        ctx.close()
+
+
+def _wait_all(ctx, tickets):
+    end = time.time() + 60.0
+    for t in tickets:
+        while ctx.poll(t) is None:
+            assert time.time() < end, "requests did not complete"
+            time.sleep(0.001)
 
 
 def test_tune_keys_checked(ctx, haze):
