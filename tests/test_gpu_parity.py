@@ -430,6 +430,31 @@ def test_few_rays_equal_the_full_launch(ctx, haze, n):
     field.release()
 
 
+@pytest.mark.parametrize("dtype,width,height", [("f32", 1021, 700), ("f16", 1021, 600), ("bf16", 1500, 1100)])
+def test_second_batches_equal_single_batches(ctx, haze, dtype, width, height):
+    """Launches with more rays than their waves hold at once (393,216: the rest
+    goes to waves that have finished, reserved late with less than a second
+    batch for each) give the bits of launches in which every ray has a lane."""
+    grid = W.make_grid((0.0, 0.0, 0.0), (0.9, 0.8, 1.1), (24, 20, 28))
+    rng = np.random.default_rng(2)
+    dn = (1e-3 * rng.standard_normal((28, 20, 24))).astype(np.float32)
+    field = ctx.index_field_from_grid(torch.from_numpy(dn).cuda(), grid, dtype=dtype,
+                                      store_scale=1.0 if dtype == "f32" else 64.0)
+    views = [W.ring_view(grid.lo, grid.hi, 0.4, 0.95, width, height, backdrop_beyond=0.6)]
+    step = W.make_steps(grid)[0]
+    full = ctx.trace_views(field, views, step)
+    hits = int((full["steps"] > 0).sum())
+    print(f"case {dtype} {width}x{height}: {hits} rays enter", flush=True)
+    assert hits > 393216
+    for lo in range(0, width * height, 300000):
+        ids = torch.arange(lo, min(lo + 300000, width * height), device="cuda")
+        sub = ctx.trace_views(field, views, step, ray_ids=ids)
+        for k, v in sub.items():
+            a, b = v.cpu().numpy(), full[k][ids].cpu().numpy()
+            assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), (k, lo)
+    field.release()
+
+
 @pytest.mark.parametrize("dtype,res", [
     ("f32", (2, 2, 2)), ("f16", (2, 2, 2)), ("bf16", (2, 2, 2)), ("f32", (5, 2, 131)), ("f16", (3, 70, 33)),
     ("bf16", (131, 2, 17)), ("f32", (67, 40, 51)), ("f16", (40, 67, 50)), ("bf16", (51, 43, 67)),
