@@ -315,7 +315,9 @@ extern "C" hz_status hz_mesh_create(hz_ctx *c, const hz_triangle *tris, int32_t 
               hipMemcpyAsync((char *)mem + off_surf, surf.data(), surf.size(), hipMemcpyHostToDevice, s) ==
                   hipSuccess &&
               hipMemcpyAsync((char *)mem + off_start, starts.data(), 4 * starts.size(), hipMemcpyHostToDevice, s) ==
-                  hipSuccess;
+                  hipSuccess &&
+              // the tracer reads list entries four at a time (triangle 0 past a shorter array)
+              hipMemsetAsync((char *)mem + off_list, 0, 16, s) == hipSuccess;
     if (ok) {
         hipLaunchKernelGGL(k_shell<true>, dim3(blocks), dim3(256), 0, s, G, (const float *)dverts, ntris,
                            (float *)nullptr, (uint32_t *)nullptr, (const uint32_t *)((char *)mem + off_start),

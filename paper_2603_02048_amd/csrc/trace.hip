@@ -66,6 +66,12 @@ __device__ __forceinline__ float quad_side(const SceneQuad &Q, const float x[3])
     return fmaf(Q.n[0], x[0], fmaf(Q.n[1], x[1], fmaf(Q.n[2], x[2], -Q.n0)));
 }
 
+// The same with the plane (n, n0) as one vector.
+__device__ __forceinline__ float plane_side(const float4 &P, const float x[3])
+{
+    return fmaf(P.x, x[0], fmaf(P.y, x[1], fmaf(P.z, x[2], -P.w)));
+}
+
 __device__ __forceinline__ bool in_quad(const SceneQuad &Q, const float h[3])
 {
     const float u = fmaf(Q.du[0], h[0], fmaf(Q.du[1], h[1], fmaf(Q.du[2], h[2], -Q.du0)));
@@ -104,18 +110,83 @@ __device__ __forceinline__ bool in_tri(const SceneQuad &T, const float h[3])
     return u >= 0.0f && v >= 0.0f && u + v <= 1.0f;
 }
 
-// Straight ray x + t w against triangle k: keeps the first hit in (best, bt),
-// ties to the lower triangle index.
-__device__ __forceinline__ void cast_tri(const MeshLaunch &M, int k, const float x[3], const float w[3], int &best,
-                                         float &bt)
+// The tests' loads are gathers, served by the texture-address unit a lane (or
+// what shares its line) at a time: list entries are read four and ranges two to
+// a load (global loads need the words' own alignment), and the planes of a mesh
+// of up to kLdsTriangles, 32 KB, come from LDS (five workgroups of the march
+// then just fit a compute unit).  The march of 2 x 640x360 with 448 triangles:
+// 136 us with the planes in memory, 126 from LDS.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(4)));
+constexpr int kLdsTriangles = 2048;
+extern __shared__ float4 mesh_planes[];
+
+// Plane (n, n0) of triangle k.
+__device__ __forceinline__ float4 tri_plane(const MeshLaunch &M, int k)
 {
-    const SceneQuad &T = M.tris[k];
-    const float dn = T.n[0] * w[0] + T.n[1] * w[1] + T.n[2] * w[2];
+    if (M.ntris <= kLdsTriangles) return mesh_planes[k];
+    return *reinterpret_cast<const float4 *>(M.tris[k].n);
+}
+
+// Fills them; all threads of the workgroup, before its first tri_plane().
+__device__ __forceinline__ void load_planes(const MeshLaunch &M)
+{
+    if (M.ntris > kLdsTriangles) return;
+    for (int k = (int)threadIdx.x; k < M.ntris; k += (int)blockDim.x)
+        mesh_planes[k] = *reinterpret_cast<const float4 *>(M.tris[k].n);
+    __syncthreads();
+}
+
+static size_t mesh_lds(const TraceLaunch &L)
+{
+    return L.mesh.ntris <= kLdsTriangles ? sizeof(float4) * (size_t)L.mesh.ntris : 0;
+}
+
+// f(k, plane) for those triangles of M.list[e0, e1), in its order, for which
+// may(plane) holds.  Sorted out 32 at a time first: a wave then takes f as often
+// as its busiest lane has candidates, not at every entry that is one for any
+// lane.  (The load of a list's last entries begins before the list where it
+// can, and reads past it in an array of less than four, which hz_mesh_create
+// fills up; neither counts.)
+template <class G, class F>
+__device__ __forceinline__ void for_list(const MeshLaunch &M, uint32_t e0, uint32_t e1, const G &may, const F &f)
+{
+    for (uint32_t b = e0; b < e1; b += 32u) {
+        const uint32_t be = min(b + 32u, e1);
+        uint32_t cand = 0u;
+        for (uint32_t e = b; e < be; e += 4u) {
+            const uint32_t g = max(min(e + 4u, e1), 4u) - 4u;
+            const u32x4 k4 = *reinterpret_cast<const u32x4 *>(M.list + g);
+            const int k[4] = {(int)k4.x, (int)k4.y, (int)k4.z, (int)k4.w};
+            float4 P[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) P[j] = tri_plane(M, k[j]);
+            uint32_t m = 0u;
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j)
+                if (may(P[j])) m |= 1u << j;
+            cand |= (m >> (e - g)) << (e - b);
+        }
+        if (be - b < 32u) cand &= (1u << (be - b)) - 1u;
+        while (cand) {
+            const int k = (int)M.list[b + (uint32_t)__builtin_ctz(cand)];
+            cand &= cand - 1u;
+            f(k, tri_plane(M, k));
+        }
+    }
+}
+
+// Straight ray x + t w against triangle k of plane P (n, n0): keeps the first
+// hit in (best, bt), ties to the lower triangle index.
+__device__ __forceinline__ void cast_tri(const MeshLaunch &M, int k, const float4 &P, const float x[3],
+                                         const float w[3], int &best, float &bt)
+{
+    const float dn = P.x * w[0] + P.y * w[1] + P.z * w[2];
     if (dn == 0.0f) return;
-    const float t = -quad_side(T, x) / dn;
+    const float t = -plane_side(P, x) / dn;
     if (!(t >= 0.0f) || t > bt || (t == bt && best >= 0 && k >= best)) return;
     const float h[3] = {fmaf(t, w[0], x[0]), fmaf(t, w[1], x[1]), fmaf(t, w[2], x[2])};
-    if (!in_tri(T, h)) return;
+    if (!in_tri(M.tris[k], h)) return;
     best = k;
     bt = t;
 }
@@ -131,7 +202,7 @@ __device__ int cast_mesh(const MeshLaunch &M, const float x[3], const float w[3]
     int best = -1;
     float bt = tmax;
     if (M.brute) {
-        for (int k = 0; k < M.ntris; ++k) cast_tri(M, k, x, w, best, bt);
+        for (int k = 0; k < M.ntris; ++k) cast_tri(M, k, tri_plane(M, k), x, w, best, bt);
         ntests += (uint32_t)M.ntris;
         thit = bt;
         return best;
@@ -179,29 +250,42 @@ __device__ int cast_mesh(const MeshLaunch &M, const float x[3], const float w[3]
     axis_start(2, cz, sz, tnz, tdz);
     const int rx = M.res[0], ry = M.res[1], rz = M.res[2];
     float tenter = ta;
+    uint32_t cell = ((uint32_t)cz * (uint32_t)ry + (uint32_t)cy) * (uint32_t)rx + (uint32_t)cx;
+    const auto cell_list = [&](uint32_t &e0, uint32_t &e1) {
+        const u32x2 se = *reinterpret_cast<const u32x2 *>(M.start + cell);
+        e0 = se.x;
+        e1 = se.y;
+    };
+    // cells left along each axis, and the steps in the cell numbers
+    int lx = sx > 0 ? rx - 1 - cx : cx, ly = sy > 0 ? ry - 1 - cy : cy, lz = sz > 0 ? rz - 1 - cz : cz;
+    const uint32_t jx = (uint32_t)sx, jy = (uint32_t)(sy * rx), jz = (uint32_t)(sz * (rx * ry));
+    uint32_t e0, e1;
+    cell_list(e0, e1);
     for (int it = 0; it < rx + ry + rz + 3; ++it) {
         if (tenter > bt) break;
-        const uint32_t cell = ((uint32_t)cz * (uint32_t)ry + (uint32_t)cy) * (uint32_t)rx + (uint32_t)cx;
-        const uint32_t e0 = M.start[cell], e1 = M.start[cell + 1];
-        for (uint32_t e = e0; e < e1; ++e) cast_tri(M, (int)M.list[e], x, w, best, bt);
-        ntests += e1 - e0;
-        if (tnx <= tny && tnx <= tnz) {
-            tenter = tnx;
-            cx += sx;
-            tnx += tdx;
-            if (cx < 0 || cx >= rx) break;
-        } else if (tny <= tnz) {
-            tenter = tny;
-            cy += sy;
-            tny += tdy;
-            if (cy < 0 || cy >= ry) break;
-        } else {
-            tenter = tnz;
-            cz += sz;
-            tnz += tdz;
-            if (cz < 0 || cz >= rz) break;
+        // the next cell, and its list's range while this cell's list is tested
+        const bool ax = tnx <= tny && tnx <= tnz, ay = !ax && tny <= tnz, az = !ax && !ay;
+        tenter = ax ? tnx : ay ? tny : tnz;
+        tnx = ax ? tnx + tdx : tnx;
+        tny = ay ? tny + tdy : tny;
+        tnz = az ? tnz + tdz : tnz;
+        cell += ax ? jx : ay ? jy : jz;
+        lx -= ax;
+        ly -= ay;
+        lz -= az;
+        const bool last = min(min(lx, ly), lz) < 0 || tenter > tb;
+        uint32_t f0 = 0u, f1 = 0u;
+        if (!last) cell_list(f0, f1);
+        for (uint32_t e = e0; e < e1; e += 2u) {
+            const int k0 = (int)M.list[e], k1 = (int)M.list[min(e + 1u, e1 - 1u)];
+            const float4 P0 = tri_plane(M, k0), P1 = tri_plane(M, k1);
+            cast_tri(M, k0, P0, x, w, best, bt);
+            cast_tri(M, k1, P1, x, w, best, bt);   // (k0 once more changes nothing)
         }
-        if (tenter > tb) break;
+        ntests += e1 - e0;
+        if (last) break;
+        e0 = f0;
+        e1 = f1;
     }
     thit = bt;
     return best;
@@ -210,17 +294,17 @@ __device__ int cast_mesh(const MeshLaunch &M, const float x[3], const float w[3]
 // The chord a -> b = a + ds w of one march step against triangle k: the side
 // value changes sign (or reaches zero) along it; keeps the first crossing
 // (fraction lam, then the lower index) in (best, bl, hp).
-__device__ __forceinline__ void chord_tri(const MeshLaunch &M, int k, const float a[3], const float b[3],
-                                          const float w[3], float ds, int &best, float &bl, float hp[3])
+__device__ __forceinline__ void chord_tri(const MeshLaunch &M, int k, const float4 &P, const float a[3],
+                                          const float b[3], const float w[3], float ds, int &best, float &bl,
+                                          float hp[3])
 {
-    const SceneQuad &T = M.tris[k];
-    const float s0 = quad_side(T, a), s1 = quad_side(T, b);
+    const float s0 = plane_side(P, a), s1 = plane_side(P, b);
     if (s0 == 0.0f || (s0 > 0.0f && s1 > 0.0f) || (s0 < 0.0f && s1 < 0.0f)) return;
     const float lam = s0 / (s0 - s1);
     if (!(lam < bl || (lam == bl && k < best))) return;
     const float back = (1.0f - lam) * ds;
     const float h[3] = {fmaf(-back, w[0], b[0]), fmaf(-back, w[1], b[1]), fmaf(-back, w[2], b[2])};
-    if (!in_tri(T, h)) return;
+    if (!in_tri(M.tris[k], h)) return;
     best = k;
     bl = lam;
     hp[0] = h[0]; hp[1] = h[1]; hp[2] = h[2];
@@ -382,11 +466,18 @@ __device__ __forceinline__ uint32_t bin_rank(int bin, uint32_t (*wcnt)[kRayBins]
     return rank;
 }
 
+// The mesh's ray generation holds 104 registers a lane: one workgroup of 1,024 to
+// a compute unit, and 450 of them (2 x 640x360) took two rounds, 53 us against 44
+// in workgroups of 256.
+template <int SCENE>
+constexpr int raygen_block = SCENE == 3 ? 256 : kRaygenBlock;
+
 // SCENE: 0 no scene, 1 boards, 3 triangle mesh (the launch's scene kind, so
 // that the common case carries no scene code).
 template <int SCENE>
-__global__ __launch_bounds__(kRaygenBlock) void k_raygen(TraceLaunch L, const TraceJob *__restrict__ jobs)
+__global__ __launch_bounds__(raygen_block<SCENE>) void k_raygen(TraceLaunch L, const TraceJob *__restrict__ jobs)
 {
+    if (SCENE == 3) load_planes(L.mesh);
     // A tile's slots run down its columns (decode_slot), but the rays that
     // miss write their outputs here, by pixel: the 64 threads of a tile take
     // its slots transposed, so neighbouring threads write neighbouring pixels
@@ -466,18 +557,18 @@ __global__ __launch_bounds__(kRaygenBlock) void k_raygen(TraceLaunch L, const Tr
         }
     }
     // the next launch's counter set (this launch's march uses the other one)
-    static_assert(kMarchHead < kRaygenBlock, "one workgroup clears a counter set");
+    static_assert(kMarchHead < raygen_block<SCENE>, "one workgroup clears a counter set");
     if (blockIdx.x == 0 && threadIdx.x <= kMarchHead) *hit_counter(L.counters_next, threadIdx.x) = 0u;
     // pass 1 of the length sort: remember the bin, count the bins of the
     // workgroup (wave ballots), one atomic per non-empty bin
     if (!enters) bin = 255;
     if (slot < L.nslots) L.slot_bin[slot] = (uint8_t)bin;
-    __shared__ uint32_t wcnt[kRaygenBlock / 64][kRayBins];
+    __shared__ uint32_t wcnt[raygen_block<SCENE> / 64][kRayBins];
     bin_rank(bin, wcnt);
     __syncthreads();
     if (threadIdx.x < kRayBins) {
         uint32_t total = 0;
-        for (int w = 0; w < kRaygenBlock / 64; ++w) total += wcnt[w][threadIdx.x];
+        for (int w = 0; w < raygen_block<SCENE> / 64; ++w) total += wcnt[w][threadIdx.x];
         if (total) atomicAdd(hit_counter(L.counters, threadIdx.x), total);
     }
 }
@@ -917,6 +1008,27 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
                     }
                 }
                 if (status < 0) {
+                    // the shell cell of C_k, its bound and list with the field's loads
+                    float shell = INFINITY;
+                    uint32_t e0 = 0u, e1 = 0u;
+                    if (SCENE == 3 && !L.mesh.brute) {
+                        const MeshLaunch &M = L.mesh;
+                        int ci[3];
+                        bool in = true;
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            ci[a] = (int)floorf((c[a] - M.lo[a]) * M.inv_cell);
+                            in = in && ci[a] >= 0 && ci[a] < M.res[a];
+                        }
+                        if (in) {
+                            const uint32_t cell = ((uint32_t)ci[2] * (uint32_t)M.res[1] + (uint32_t)ci[1]) *
+                                                      (uint32_t)M.res[0] + (uint32_t)ci[0];
+                            shell = M.dlow[cell];
+                            const u32x2 se = *reinterpret_cast<const u32x2 *>(M.start + cell);
+                            e0 = se.x;
+                            e1 = se.y;
+                        }
+                    }
                     const float4 s = sample_field<DT, ONE>(G, K, rows, field, c);
                     const float n = 1.0f + s.x;
                     const float rn = __builtin_amdgcn_rcpf(n);
@@ -971,26 +1083,15 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
                         const MeshLaunch &M = L.mesh;
                         float bl = 2.0f;
                         if (M.brute) {
-                            for (int k = 0; k < M.ntris; ++k) chord_tri(M, k, cp, c, w, ds, surf, bl, hp);
+                            for (int k = 0; k < M.ntris; ++k)
+                                chord_tri(M, k, tri_plane(M, k), cp, c, w, ds, surf, bl, hp);
                             ntests += (uint32_t)M.ntris;
-                        } else {
-                            int ci[3];
-                            bool in = true;
-#pragma unroll
-                            for (int a = 0; a < 3; ++a) {
-                                ci[a] = (int)floorf((cp[a] - M.lo[a]) * M.inv_cell);
-                                in = in && ci[a] >= 0 && ci[a] < M.res[a];
-                            }
-                            if (in) {
-                                const uint32_t cell = ((uint32_t)ci[2] * (uint32_t)M.res[1] + (uint32_t)ci[1]) *
-                                                          (uint32_t)M.res[0] + (uint32_t)ci[0];
-                                if (M.dlow[cell] <= ds * 1.001f) {
-                                    const uint32_t e0 = M.start[cell], e1 = M.start[cell + 1];
-                                    for (uint32_t e = e0; e < e1; ++e)
-                                        chord_tri(M, (int)M.list[e], cp, c, w, ds, surf, bl, hp);
-                                    ntests += e1 - e0;
-                                }
-                            }
+                        } else if (shell <= ds * 1.001f) {
+                            for_list(
+                                M, e0, e1,
+                                [&](const float4 &P) { return plane_side(P, cp) * plane_side(P, c) <= 0.0f; },
+                                [&](int k, const float4 &P) { chord_tri(M, k, P, cp, c, w, ds, surf, bl, hp); });
+                            ntests += e1 - e0;
                         }
                     }
                     if (SCENE == 2) {
@@ -1068,6 +1169,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 template <int DT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_march_mesh(TraceLaunch L)
 {
+    load_planes(L.mesh);
     march<DT, 3, false>(L);
 }
 
@@ -1117,7 +1219,8 @@ hipError_t launch_raygen(const TraceLaunch &L, bool clear_counters, hipStream_t 
     const dim3 g((unsigned)((L.nslots + kRaygenBlock - 1) / kRaygenBlock));
     hipEvent_t e0 = clear_counters ? nullptr : t.start;
     if (L.mesh.ntris > 0)
-        hipExtLaunchKernelGGL(k_raygen<3>, g, dim3(kRaygenBlock), 0, s, e0, nullptr, 0, L, L.jobs);
+        hipExtLaunchKernelGGL(k_raygen<3>, dim3((unsigned)((L.nslots + raygen_block<3> - 1) / raygen_block<3>)),
+                              dim3(raygen_block<3>), mesh_lds(L), s, e0, nullptr, 0, L, L.jobs);
     else if (L.nquads > 0)
         hipExtLaunchKernelGGL(k_raygen<1>, g, dim3(kRaygenBlock), 0, s, e0, nullptr, 0, L, L.jobs);
     else
@@ -1135,8 +1238,8 @@ static void launch_march_t(const TraceLaunch &L, int march_blocks, hipStream_t s
         hipExtLaunchKernelGGL((march_kernel<DT, SCENE, one_field_march<SCENE>>()), dim3(march_blocks), dim3(256), 0, s,
                               t.start, t.stop, 0, L);
     else
-        hipExtLaunchKernelGGL((march_kernel<DT, SCENE, false>()), dim3(march_blocks), dim3(256), 0, s, t.start, t.stop,
-                              0, L);
+        hipExtLaunchKernelGGL((march_kernel<DT, SCENE, false>()), dim3(march_blocks), dim3(256),
+                              SCENE == 3 ? mesh_lds(L) : 0, s, t.start, t.stop, 0, L);
 }
 
 template <int DT>

@@ -133,6 +133,34 @@ def test_mesh_shell_changes_no_result(ctx, haze):
     field.release()
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 31, 33, 70, 2047, 2048, 2049])
+def test_mesh_list_lengths_change_no_result(ctx, haze, n):
+    """Lists of one to hundreds of entries (read in fours, sorted out 32 at a
+    time), arrays of less than four, and planes in LDS (up to 2,048 triangles)
+    or memory: the bits of the brute-force mesh."""
+    wl = W.make_small(seed=15, width=48, height=36, nviews=2).with_k_gd(200.0)
+    print(f"case mesh of {n} triangles in one clump", flush=True)
+    field = ctx.splat_index_field(haze.upload_particles(wl.particles), wl.grid, wl.k_gd, wl.h)
+    views = _views(wl.grid.lo, wl.grid.hi, n=2, width=48, height=36)
+    rng = np.random.default_rng(n)
+    size = 0.12 if n < 100 else 0.03
+    centre = 0.5 * (wl.grid.lo + wl.grid.hi) + 0.03 * rng.standard_normal((n, 1, 3))
+    tris = (centre + size * rng.standard_normal((n, 3, 3))).astype(np.float32)
+    surf = rng.integers(0, 200, n)
+    reach = wl.step_adaptive.ds_max
+    outs = []
+    for cell in (0.0, 1.3 * reach):
+        for brute in (False, True):
+            m = ctx.mesh_create(tris, surf, reach=reach, cell=cell, brute_force=brute)
+            outs.append(to_np(ctx.trace_mesh(field, views, m, wl.step_adaptive)))
+            m.release()
+    assert ((outs[0]["surface"] > 0) & (outs[0]["surface"] < 255)).any()
+    for o in outs[1:]:
+        for k in o:
+            assert np.array_equal(o[k].view(np.uint8), outs[0][k].view(np.uint8)), k
+    field.release()
+
+
 def test_mesh_sphere_inside_volume(ctx, haze):
     wl = W.make_small(seed=13, width=64, height=48, nviews=1).with_k_gd(200.0)
     print("case mesh sphere of 320 triangles inside the volume", flush=True)
