@@ -55,6 +55,17 @@ __device__ __forceinline__ int cell_coord(float x, float clo, float inv_cell, in
     return (int)c;
 }
 
+// The cell of a particle; none (~0) outside the grown box or with a mass that
+// is not finite: such a particle adds nothing.
+__device__ __forceinline__ uint32_t cell_of_particle(const CellGrid &cg, float x, float y, float z, float m)
+{
+    const int cx = cell_coord(x, cg.clo[0], cg.inv_cell, cg.nc[0]);
+    const int cy = cell_coord(y, cg.clo[1], cg.inv_cell, cg.nc[1]);
+    const int cz = cell_coord(z, cg.clo[2], cg.inv_cell, cg.nc[2]);
+    if (cx < 0 || cy < 0 || cz < 0 || !isfinite(m)) return 0xffffffffu;
+    return (uint32_t)((cz * cg.nc[1] + cy) * cg.nc[0] + cx);
+}
+
 // Dispatch order of the gather's bricks, heaviest first, in two phases that
 // each run in one extra 256-thread workgroup of a cell-list kernel, beside
 // that kernel's own work.  bwork[b] is the number of candidate particles
@@ -179,17 +190,11 @@ __global__ __launch_bounds__(256) void k_cell_count(const float *__restrict__ x,
     if (i == 0) *fail = 0u;
     uint32_t mbits = 0u;
     if (i < n) {
-        const int cx = cell_coord(x[i], cg.clo[0], cg.inv_cell, cg.nc[0]);
-        const int cy = cell_coord(y[i], cg.clo[1], cg.inv_cell, cg.nc[1]);
-        const int cz = cell_coord(z[i], cg.clo[2], cg.inv_cell, cg.nc[2]);
-        // a particle outside the grown box, or with a mass that is not
-        // finite, is in no cell and adds nothing
-        const float am = fabsf(m[i]);
-        uint32_t id = 0xffffffffu;
-        if (cx >= 0 && cy >= 0 && cz >= 0 && isfinite(am)) {
-            id = (uint32_t)((cz * cg.nc[1] + cy) * cg.nc[0] + cx);
+        const float mi = m[i];
+        const uint32_t id = cell_of_particle(cg, x[i], y[i], z[i], mi);
+        if (id != 0xffffffffu) {
             lrank[i] = atomicAdd(&count[id], 1u);
-            if (MMAX && am > 0.0f) mbits = __float_as_uint(am);
+            if (MMAX && fabsf(mi) > 0.0f) mbits = __float_as_uint(fabsf(mi));
         }
         cid[i] = id;
     }
@@ -367,6 +372,88 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_onepass(uint32_t *__restr
         run += v[k];
     }
     if (tile == ntiles - 1 && threadIdx.x == SCAN_THREADS - 1) start[n] = run;
+}
+
+// The whole cell list of few particles over few cells in one workgroup and one
+// launch, the counts, starts and slots in LDS: the same start and sorted
+// contents as k_cell_count to k_cell_order, whose four launches cost more than
+// their work here: 3,000 particles over 3,600 cells 19.7 us of the device
+// against 8.5, 300 over 700 18 against 5, and three launches less of the
+// host's time.  The limits are where one workgroup is still clearly faster
+// (with 8 particles a thread 8,000 took 16 us against 20, but 3,000 took 12);
+// counts and slots of that many take 48 KB.  There is no wait that could fail.
+constexpr int SMALL_THREADS = 1024;
+constexpr int SMALL_PER_THREAD = 4;
+constexpr int SMALL_PARTS = SMALL_THREADS * SMALL_PER_THREAD;
+constexpr int SMALL_CELLS_PER_THREAD = 8;
+constexpr int SMALL_CELLS = SMALL_THREADS * SMALL_CELLS_PER_THREAD;
+
+__global__ __launch_bounds__(SMALL_THREADS) void k_cells_small(const float *__restrict__ x, const float *__restrict__ y,
+                                                               const float *__restrict__ z, const float *__restrict__ m,
+                                                               int32_t n, CellGrid cg, uint32_t *__restrict__ start,
+                                                               float4 *__restrict__ sorted, uint32_t *__restrict__ fail,
+                                                               int32_t mass_root)
+{
+    __shared__ uint32_t cell[SMALL_CELLS + 1];   // counts, then starts
+    __shared__ uint32_t slots[SMALL_PARTS];
+    __shared__ uint32_t wave_tot[SMALL_THREADS / 64];
+    const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+    for (int c = t; c < cg.ncells; c += SMALL_THREADS) cell[c] = 0u;
+    if (t == 0) *fail = 0u;
+    float4 rec[SMALL_PER_THREAD];
+    uint32_t id[SMALL_PER_THREAD], at[SMALL_PER_THREAD];
+#pragma unroll
+    for (int k = 0; k < SMALL_PER_THREAD; ++k) {
+        const int i = k * SMALL_THREADS + t;
+        rec[k] = i < n ? make_float4(x[i], y[i], z[i], m[i]) : make_float4(0.0f, 0.0f, 0.0f, __builtin_nanf(""));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SMALL_PER_THREAD; ++k) {
+        id[k] = cell_of_particle(cg, rec[k].x, rec[k].y, rec[k].z, rec[k].w);
+        at[k] = id[k] != 0xffffffffu ? atomicAdd(&cell[id[k]], 1u) : 0u;
+    }
+    __syncthreads();
+    // exclusive scan: eight cells a thread, then the waves, then the workgroup
+    uint32_t v[SMALL_CELLS_PER_THREAD], sum = 0u;
+#pragma unroll
+    for (int k = 0; k < SMALL_CELLS_PER_THREAD; ++k) {
+        const int c = t * SMALL_CELLS_PER_THREAD + k;
+        v[k] = c < cg.ncells ? cell[c] : 0u;
+        sum += v[k];
+    }
+    uint32_t run = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t up = __shfl_up(run, d);
+        if (lane >= d) run += up;
+    }
+    if (lane == 63) wave_tot[wave] = run;
+    __syncthreads();
+    run -= sum;
+    for (int w = 0; w < wave; ++w) run += wave_tot[w];
+#pragma unroll
+    for (int k = 0; k < SMALL_CELLS_PER_THREAD; ++k) {
+        const int c = t * SMALL_CELLS_PER_THREAD + k;
+        if (c < cg.ncells) cell[c] = run;
+        run += v[k];
+    }
+    if (t == SMALL_THREADS - 1) cell[cg.ncells] = run;   // the total
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SMALL_PER_THREAD; ++k)
+        if (id[k] != 0xffffffffu) slots[cell[id[k]] + at[k]] = (uint32_t)(k * SMALL_THREADS + t);
+    for (int c = t; c <= cg.ncells; c += SMALL_THREADS) start[c] = cell[c];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SMALL_PER_THREAD; ++k) {
+        if (id[k] == 0xffffffffu) continue;
+        const uint32_t b = cell[id[k]], e = cell[id[k] + 1];
+        uint32_t rank = 0u;
+        for (uint32_t j = b; j < e; ++j) rank += slots[j] < (uint32_t)(k * SMALL_THREADS + t) ? 1u : 0u;
+        if (mass_root) rec[k].w = (float)cbrt((double)rec[k].w);
+        sorted[b + rank] = rec[k];
+    }
 }
 
 // Every binned particle takes the slot of its cell given by its arrival rank
@@ -1458,6 +1545,11 @@ hipError_t launch_cell_list(const float *x, const float *y, const float *z, cons
                               nullptr, 0, (uint32_t *)scan, 0u, words);
         first = false;
         *scan_base = 0;
+    }
+    if (n <= SMALL_PARTS && cg.ncells <= SMALL_CELLS && !want_mmax && !bwork && guard.tag_bias == 0) {
+        hipExtLaunchKernelGGL(k_cells_small, dim3(1), dim3(SMALL_THREADS), 0, s, first ? t.start : nullptr, t.stop, 0, x,
+                              y, z, m, n, cg, start, sorted, fail, mass_root ? 1 : 0);
+        return hipGetLastError();
     }
     if (want_mmax)
         hipExtLaunchKernelGGL(k_cell_count<true>, dim3(blocks_for(n, 256)), dim3(256), 0, s,

@@ -116,6 +116,34 @@ def test_splat_tiles_parity(ctx, haze, res, h, n, signs):
     again.release()
 
 
+@pytest.mark.parametrize("n,h", [(1, 0.03), (2, 0.2), (63, 0.03), (1023, 0.0268), (1025, 0.03), (4095, 0.0268),
+                                 (4096, 0.0266), (4096, 0.03)])
+def test_small_cell_list_equals_the_large(ctx, haze, n, h):
+    """Up to 4,096 particles over 8,192 cells are binned in one launch: the bits
+    of the same particles followed by others that are in no cell, which take
+    the general way (h = 0.0268 gives 8,160 cells, 0.0266 8,568)."""
+    wl = W.make_small(seed=31, res=(19, 15, 11), h=h, n=max(n, 2))
+    p = wl.particles
+    x, y, z, m = (np.array(a[:n], np.float32) for a in (p.x, p.y, p.z, p.m))
+    if n > 1000:   # outside the box, and without a usable mass
+        x[5::97] = 9.0
+        m[7::89] = np.nan
+        m[11::83] *= -1.0
+
+    def splat(extra):
+        far = np.full(extra, 50.0, np.float32)
+        parts = haze.upload_particles(W.Particles(*(np.concatenate([a, far]) for a in (x, y, z, m))))
+        f = ctx.splat_index_field(parts, wl.grid, wl.k_gd, wl.h)
+        out = _field_np(ctx, f)
+        f.release()
+        return out
+
+    a, b = splat(0), splat(4200)
+    assert np.abs(a[0]).max() > 0.0
+    for u, v in zip(a, b):
+        assert np.array_equal(u.view(np.uint32), v.view(np.uint32))
+
+
 @pytest.mark.parametrize("method", ["gather", "gather8", "scatter"])
 def test_splat_is_bitwise_repeatable(ctx, haze, method):
     _use(ctx, method)
