@@ -787,6 +787,7 @@ __global__ __launch_bounds__(64 * SPLAT_WAVES) void k_splat(SplatParams P, const
 // Each wave owns an octant of 4 x 4 x 4 voxels (a workgroup of four waves a
 // brick of 8 x 8 x 4; the waves never meet) and sums its two blocks of
 // 4 x 4 x 2 together:
+// (In small launches the four waves of a workgroup share one octant.)
 //   1. It holds the octant's cell-list row ranges in its lanes (8 x 8 rows at a
 //      time) and reads the rows' particles 64 at a time, one per lane, packing
 //      short rows into one read, and one read ahead.
@@ -811,9 +812,10 @@ __global__ __launch_bounds__(64 * SPLAT_WAVES) void k_splat(SplatParams P, const
 // the FP32 MFMA does not run beside the VALU (8 cycles a slot, against 6 here).
 // Measured, column gather to tiles: 1,048,576 particles on 256^3 voxels 2,060
 // to 1,750 us; 262,144 on 128^3 320 to 245; 16,384 on 64^3 36 to 19; 3,000 on
-// 21x17x13 71 to 18 (here the column gather walks its rows one after another).
+// 21x17x13 71 to 12 (here the column gather walks its rows one after another).
 // Every sum runs in a fixed order (ring order within a lane, then the sixteen
-// lanes), so the field is bitwise repeatable.
+// lanes, then the waves that share an octant), so the field is bitwise
+// repeatable.
 constexpr int TILE_BX = 8, TILE_BY = 8, TILE_BZ = 4;   // a workgroup's voxels
 constexpr int TILE_RING = 80;                          // ring entries: 15 left over + 64 appended, in whole tiles
 
@@ -928,19 +930,22 @@ __device__ __forceinline__ void halve(float *v, int lane)
     }
 }
 
+// SPLIT: a workgroup takes one octant, its waves every fourth 64 particles each.
+template <bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6)))
 void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const float4 *__restrict__ parts,
                    int32_t nbricks, float *__restrict__ dn, const uint32_t *__restrict__ fail)
 {
     // per wave: outer and inner ring of block 0, outer and inner ring of block 1
     __shared__ float4 rings[4][4 * TILE_RING];
-    const int32_t brick = (int32_t)blockIdx.x;
+    const int32_t brick = (int32_t)(SPLIT ? blockIdx.x >> 2 : blockIdx.x);
     if (brick >= nbricks) return;
     const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t oct = SPLIT ? (int32_t)(blockIdx.x & 3u) : wave;
     const int lane = threadIdx.x & 63, comp = lane >> 4;
-    const int32_t o0[3] = {brick % P.nbx * TILE_BX + 4 * (wave & 1), brick / P.nbx % P.nby * TILE_BY + 4 * (wave >> 1),
+    const int32_t o0[3] = {brick % P.nbx * TILE_BX + 4 * (oct & 1), brick / P.nbx % P.nby * TILE_BY + 4 * (oct >> 1),
                            brick / (P.nbx * P.nby) * TILE_BZ};
-    if (o0[0] >= P.res[0] || o0[1] >= P.res[1]) return;   // (waves never meet at a barrier)
+    if (o0[0] >= P.res[0] || o0[1] >= P.res[1]) return;   // (the waves of an octant together)
     // Positions below are from the octant's centre in units of 2h: x = p scale +
     // c, with c the rounded -(centre) scale; what rounding took from c is taken
     // off the voxels too.
@@ -987,7 +992,7 @@ void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const floa
     uint64_t todo = 0ull;
     uint32_t cs = 0u, ce = 0u;
     // the next particles of the rows, one per lane; returns how many lanes have one
-    const auto next = [&](float4 &q) -> uint32_t {
+    const auto next = [&](float4 &q, bool read = true) -> uint32_t {
         uint32_t at = 0u, filled = 0u;
         while (filled < 64u) {
             if (cs == ce) {
@@ -1027,9 +1032,15 @@ void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const floa
             cs += take;
             filled += take;
         }
+        if (!read) return filled;
         q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (__builtin_amdgcn_inverse_ballot_w64(lanes_below(filled))) q = parts[at];
         return filled;
+    };
+    // passes over the other waves' particles
+    const auto skip = [&](int32_t times) {
+        float4 none;
+        for (int32_t k = 0; k < times; ++k) next(none, false);
     };
 
     float4 *const my = rings[wave];
@@ -1059,9 +1070,11 @@ void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const floa
         wave_lds_fence();
     };
     float4 q, q_next;
+    if (SPLIT) skip(wave);
     uint32_t cnt = next(q);
 #pragma unroll 1
     while (cnt) {
+        if (SPLIT) skip(3);
         const uint32_t cnt_next = next(q_next);
         const float x = fmaf(q.x, T.scale, c[0]), y = fmaf(q.y, T.scale, c[1]), z = fmaf(q.z, T.scale, c[2]);
         const float ex = clamp01(fabsf(x) - half[0]), ey = clamp01(fabsf(y) - half[1]);
@@ -1101,6 +1114,14 @@ void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const floa
     halve<4, 0x141>(sum, lane);   // row_half_mirror, ^ 7
     halve<2, 0x1b>(sum, lane);    // quad_perm:[3,2,1,0], ^ 3
     halve<1, 0xb1>(sum, lane);    // quad_perm:[1,0,3,2], ^ 1
+    if (SPLIT) {
+        __shared__ float part[3][64];
+        if (wave > 0) part[wave - 1][lane] = sum[0];
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int w = 0; w < 3; ++w) sum[0] += part[w][lane];
+    }
     const int32_t vx = o0[0] + (lane & 3), vy = o0[1] + comp, vz = o0[2] + ((lane >> 2) & 3);
     if (vx < P.res[0] && vy < P.res[1] && vz < P.res[2])
         dn[((int64_t)vy * P.res[0] + vx) * P.res[2] + vz] = bad ? __builtin_nanf("") : sum[0] * (2.0f * P.scale);
@@ -1589,8 +1610,16 @@ hipError_t launch_splat(const SplatParams &P, const uint32_t *start, const float
 {
     const int32_t nbricks = P.nbx * P.nby * P.nbz;
     const dim3 g((unsigned)nbricks), b(64 * SPLAT_WAVES);
-    if (P.tiles)
-        hipExtLaunchKernelGGL(k_splat_tiles, g, dim3(256), 0, s, t.start, t.stop, 0, P, start, sorted, nbricks, dn,
+    // Up to 256 bricks (1,024 octants, one wave to a SIMD) the launch lasts as
+    // long as one octant's particles take a wave: there four waves share them.
+    // One wave / four: 21x17x13 voxels, 3,000 particles 19.0 / 11.7 us; 32^3,
+    // 8,000 15.7 / 12.5; 40^3 (250 bricks), 8,000 19.8 / 16.2; 48^3, 16,384
+    // 19.3 / 22.4; 64^3, 60,000 50 / 61.
+    if (P.tiles && nbricks <= 256)
+        hipExtLaunchKernelGGL(k_splat_tiles<true>, dim3(4u * (unsigned)nbricks), dim3(256), 0, s, t.start, t.stop, 0, P,
+                              start, sorted, nbricks, dn, fail);
+    else if (P.tiles)
+        hipExtLaunchKernelGGL(k_splat_tiles<false>, g, dim3(256), 0, s, t.start, t.stop, 0, P, start, sorted, nbricks, dn,
                               fail);
     else if (P.bz == 8)
         hipExtLaunchKernelGGL(k_splat<8>, g, b, 0, s, t.start, t.stop, 0, P, start, sorted, nbricks, dn,

@@ -97,11 +97,14 @@ def test_splat_parity_small(ctx, haze, seed, res, h, method):
 # the default gather at the edges of its octants of 4 x 4 x 4 voxels and blocks
 # of 4 x 4 x 2 (one voxel past them, one short of them, two voxels in all), at
 # coarse and fine voxels against h, at more rows of cells and more particles
-# per cell than a wave reads at once, and at mixed signs of the masses
+# per cell than a wave reads at once, and at mixed signs of the masses; up to
+# 256 bricks of 8x8x4 four waves share an octant, past them each has its own
 @pytest.mark.parametrize("res,h,n,signs", [((2, 2, 2), 0.2, 400, 1), ((5, 4, 3), 0.05, 3000, 1),
                                            ((4, 9, 7), 0.04, 3000, 1), ((21, 17, 13), 0.03, 6000, 1),
                                            ((8, 8, 6), 0.006, 6000, 1), ((33, 30, 41), 0.02, 20000, 1),
-                                           ((12, 10, 9), 0.3, 20000, 1), ((13, 24, 6), 0.03, 6000, -1)])
+                                           ((12, 10, 9), 0.3, 20000, 1), ((13, 24, 6), 0.03, 6000, -1),
+                                           ((64, 64, 15), 0.02, 6000, 1), ((65, 64, 15), 0.02, 6000, 1),
+                                           ((45, 46, 43), 0.015, 6000, -1), ((130, 129, 3), 0.1, 9000, 1)])
 def test_splat_tiles_parity(ctx, haze, res, h, n, signs):
     wl = W.make_small(seed=21, res=res, h=h, n=n)
     if signs < 0:
