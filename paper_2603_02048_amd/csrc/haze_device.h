@@ -192,6 +192,7 @@ struct TraceLaunch {
     int32_t ninner;        // boards that may cross the volume: tested on every step
     uint32_t inner_idx;    // their indices, one byte each (lowest byte first)
     const SceneQuad *quads;  // device copy of the nquads boards
+    float4 inner[kMaxInner];   // planes (n, n0) of the boards inner_idx names
     MeshLaunch mesh;       // triangle-mesh scene (mesh.ntris > 0), exclusive of boards
 };
 

@@ -1275,6 +1275,7 @@ static hz_status make_scene(const hz_scene *scene, const hz_grid &g, TraceLaunch
         if (overlap) {
             if (L->ninner == kMaxInner)
                 return fail(HZ_E_UNSUPPORTED, "%s: more than %d boards within a voxel of the volume", fn, kMaxInner);
+            L->inner[L->ninner] = make_float4(Q.n[0], Q.n[1], Q.n[2], Q.n0);
             L->inner_idx |= (uint32_t)k << (8 * L->ninner);
             ++L->ninner;
         }

@@ -81,13 +81,13 @@ __device__ __forceinline__ bool in_quad(const SceneQuad &Q, const float h[3])
 
 // First board met by the straight ray x + t w, t in [0, tmax]; ties go to the
 // lower index.  Returns the board index or -1, and t.
-__device__ __forceinline__ int cast_quads(const TraceLaunch &L, const float x[3], const float w[3], float tmax,
-                                          float &thit)
+__device__ __forceinline__ int cast_quads(const SceneQuad *quads, int nquads, const float x[3], const float w[3],
+                                          float tmax, float &thit)
 {
     int best = -1;
     float bt = tmax;
-    for (int k = 0; k < L.nquads; ++k) {
-        const SceneQuad &Q = L.quads[k];
+    for (int k = 0; k < nquads; ++k) {
+        const SceneQuad &Q = quads[k];
         const float dn = Q.n[0] * w[0] + Q.n[1] * w[1] + Q.n[2] * w[2];
         if (dn == 0.0f) continue;
         const float t = -quad_side(Q, x) / dn;
@@ -325,7 +325,7 @@ __device__ __forceinline__ uint32_t *tri_tests_of(const TraceLaunch &L, const Ra
 // is a triangle, reported by its surface id, and ntests counts the exact
 // triangle tests the ray took so far).
 template <int SCENE>
-__device__ __forceinline__ void finish_ray(const TraceLaunch &L, const TraceJob &J, const Ray &r, const float x[3],
+__device__ __forceinline__ void finish_ray(const TraceLaunch &L, const SceneQuad *quads, const TraceJob &J, const Ray &r, const float x[3],
                                            const float w[3], uint32_t steps, int status, const float *hp = nullptr,
                                            int surf = -1, uint32_t ntests = 0u)
 {
@@ -351,7 +351,7 @@ __device__ __forceinline__ void finish_ray(const TraceLaunch &L, const TraceJob 
             sid = 0;
             if (BOARDS) {
                 float tq;
-                const int q = cast_quads(L, x, w, hit ? tb : INFINITY, tq);
+                const int q = cast_quads(quads, L.nquads, x, w, hit ? tb : INFINITY, tq);
                 if (q >= 0) {
                     t = tq;
                     hit = true;
@@ -468,14 +468,17 @@ __device__ __forceinline__ uint32_t bin_rank(int bin, uint32_t (*wcnt)[kRayBins]
 
 // The mesh's ray generation holds 104 registers a lane: one workgroup of 1,024 to
 // a compute unit, and 450 of them (2 x 640x360) took two rounds, 53 us against 44
-// in workgroups of 256.
+// in workgroups of 256.  The others: 8 x 1280x720 55.0 us in 1,024, 51.4 in 512,
+// 49.6 in 256, but 4 x 1920x1080 51.4, 49.5 and 65.8 (each workgroup adds to the
+// same counters).
 template <int SCENE>
-constexpr int raygen_block = SCENE == 3 ? 256 : kRaygenBlock;
+constexpr int raygen_block = SCENE == 3 ? 256 : 512;
 
 // SCENE: 0 no scene, 1 boards, 3 triangle mesh (the launch's scene kind, so
 // that the common case carries no scene code).
 template <int SCENE>
-__global__ __launch_bounds__(raygen_block<SCENE>) void k_raygen(TraceLaunch L, const TraceJob *__restrict__ jobs)
+__global__ __launch_bounds__(raygen_block<SCENE>) void k_raygen(TraceLaunch L, const TraceJob *__restrict__ jobs,
+                                                                const SceneQuad *__restrict__ quads)
 {
     if (SCENE == 3) load_planes(L.mesh);
     // A tile's slots run down its columns (decode_slot), but the rays that
@@ -505,25 +508,25 @@ __global__ __launch_bounds__(raygen_block<SCENE>) void k_raygen(TraceLaunch L, c
                 const int q = cast_mesh(L.mesh, J.eye, d, t0, tq, nt);
                 if (q >= 0) {
                     const float hp[3] = {J.eye[0] + tq * d[0], J.eye[1] + tq * d[1], J.eye[2] + tq * d[2]};
-                    finish_ray<3>(L, J, r, J.eye, d, 0u, 0, hp, q, nt);
+                    finish_ray<3>(L, quads, J, r, J.eye, d, 0u, 0, hp, q, nt);
                     enters = false;
                 } else if (uint32_t *tt = tri_tests_of(L, r)) {
                     tt[r.out] = nt;
                 }
             } else {
-                finish_ray<3>(L, J, r, J.eye, d, 0u, 0);
+                finish_ray<3>(L, quads, J, r, J.eye, d, 0u, 0);
             }
         } else if (SCENE == 1 && enters) {
             // a board in front of the volume ends the ray before it enters
             float tq;
-            const int q = cast_quads(L, J.eye, d, t0, tq);
+            const int q = cast_quads(quads, L.nquads, J.eye, d, t0, tq);
             if (q >= 0) {
                 const float hp[3] = {J.eye[0] + tq * d[0], J.eye[1] + tq * d[1], J.eye[2] + tq * d[2]};
-                finish_ray<1>(L, J, r, J.eye, d, 0u, 0, hp, q);
+                finish_ray<1>(L, quads, J, r, J.eye, d, 0u, 0, hp, q);
                 enters = false;
             }
         } else if (!enters) {
-            finish_ray<SCENE == 1 ? 1 : 0>(L, J, r, J.eye, d, 0u, 0);
+            finish_ray<SCENE == 1 ? 1 : 0>(L, quads, J, r, J.eye, d, 0u, 0);
         }
     };
     if (!L.subset) {
@@ -918,7 +921,7 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
         const uint32_t nidle = (uint32_t)__popcll(idle);
         if (!done) {
             if (fin >= 0) {
-                finish_ray<SCENE>(L, L.jobs[r.job], r, c, w, steps, fin, c, fin_surf, ntests);
+                finish_ray<SCENE>(L, L.quads, L.jobs[r.job], r, c, w, steps, fin, c, fin_surf, ntests);
                 fin = -1;
             }
             if (next == end) {
@@ -968,7 +971,7 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
                     if (SCENE == 2) {
 #pragma unroll
                         for (int j = 0; j < kMaxInner; ++j)
-                            side[j] = j < L.ninner ? quad_side(L.quads[(L.inner_idx >> (8 * j)) & 255u], c) : 0.0f;
+                            side[j] = j < L.ninner ? plane_side(L.inner[j], c) : 0.0f;
                     }
                 }
             }
@@ -983,7 +986,7 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
             }
         }
         if (done && __ballot(active) == 0ull) {
-            if (fin >= 0) finish_ray<SCENE>(L, L.jobs[r.job], r, c, w, steps, fin, c, fin_surf, ntests);
+            if (fin >= 0) finish_ray<SCENE>(L, L.quads, L.jobs[r.job], r, c, w, steps, fin, c, fin_surf, ntests);
             break;
         }
         // once nothing is left to hand out, step until every lane is done
@@ -1095,6 +1098,9 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
                         }
                     }
                     if (SCENE == 2) {
+                        // (The planes come with the kernel's arguments, in scalar registers:
+                        // from memory they were a vector load and its wait per board and
+                        // step, 98 us of march at 2 x 960x540 with two boards against 87.)
                         // chord C_k -> C_{k+1} = C_{k+1} - ds w: the board whose side value
                         // changes sign (or reaches zero) first along it; ties go to the
                         // lower board index
@@ -1103,7 +1109,7 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
                         for (int j = 0; j < kMaxInner; ++j) {
                             if (j >= L.ninner) continue;
                             const int k = (int)((L.inner_idx >> (8 * j)) & 255u);
-                            const float s0 = side[j], s1 = quad_side(L.quads[k], c);
+                            const float s0 = side[j], s1 = plane_side(L.inner[j], c);
                             side[j] = s1;
                             if (s0 == 0.0f || (s0 > 0.0f && s1 > 0.0f) || (s0 < 0.0f && s1 < 0.0f)) continue;
                             const float lam = s0 / (s0 - s1);
@@ -1211,6 +1217,14 @@ hipError_t launch_put_table(void *dst, const void *src, size_t bytes, hipStream_
 // Ray generation for L.nslots > 0 slots; `clear_counters` when the set
 // L.counters was not cleared by the previous launch's ray generation (new
 // memory, or after a failed launch).
+template <int SCENE>
+static void launch_raygen_t(const TraceLaunch &L, size_t lds, hipStream_t s, hipEvent_t e0)
+{
+    constexpr int B = raygen_block<SCENE>;
+    hipExtLaunchKernelGGL(k_raygen<SCENE>, dim3((unsigned)((L.nslots + B - 1) / B)), dim3(B), lds, s, e0, nullptr, 0, L,
+                          L.jobs, L.quads);
+}
+
 hipError_t launch_raygen(const TraceLaunch &L, bool clear_counters, hipStream_t s, const KTimer &t)
 {
     if (L.nslots <= 0) return hipSuccess;
@@ -1219,12 +1233,11 @@ hipError_t launch_raygen(const TraceLaunch &L, bool clear_counters, hipStream_t 
     const dim3 g((unsigned)((L.nslots + kRaygenBlock - 1) / kRaygenBlock));
     hipEvent_t e0 = clear_counters ? nullptr : t.start;
     if (L.mesh.ntris > 0)
-        hipExtLaunchKernelGGL(k_raygen<3>, dim3((unsigned)((L.nslots + raygen_block<3> - 1) / raygen_block<3>)),
-                              dim3(raygen_block<3>), mesh_lds(L), s, e0, nullptr, 0, L, L.jobs);
+        launch_raygen_t<3>(L, mesh_lds(L), s, e0);
     else if (L.nquads > 0)
-        hipExtLaunchKernelGGL(k_raygen<1>, g, dim3(kRaygenBlock), 0, s, e0, nullptr, 0, L, L.jobs);
+        launch_raygen_t<1>(L, 0, s, e0);
     else
-        hipExtLaunchKernelGGL(k_raygen<0>, g, dim3(kRaygenBlock), 0, s, e0, nullptr, 0, L, L.jobs);
+        launch_raygen_t<0>(L, 0, s, e0);
     hipExtLaunchKernelGGL(k_raygen_place, g, dim3(kRaygenBlock), 0, s, nullptr, t.stop, 0, L);
     return hipGetLastError();
 }
