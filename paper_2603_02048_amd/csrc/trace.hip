@@ -847,21 +847,15 @@ __device__ __forceinline__ float face_distance(const TraceGrid &G, const float c
 // every step is tested against those (L.ninner of them) and the first one
 // crossed ends the ray at the crossing point.
 // ONE: every ray reads field L.field (see FieldRows), else its view's.
-template <int DT, int SCENE, bool ONE>
+template <int DT, int SCENE, bool ONE, bool LEAN>
 __device__ __forceinline__ void march(const TraceLaunch &L)
 {
     const TraceGrid &G = L.grid;
     const TraceStep &S = L.step;
     const MarchConst K = march_const<DT>(G, S);
     const FieldRows rows = ONE ? field_rows<DT>(G, L.field) : FieldRows{};
-    // The 16-bit march of the volume alone is bound by instruction issue: a
-    // step there asks once per wave whether any ray is near a face and once per
-    // ray whether anything ends it, and sorts these out only then (4 x 1920x1080
-    // of 256^3 F16: 3,320 us against 3,510).  The F32 march is bound by its
-    // gathers, and with a scene by the scene's tests: both lose by it (8 x
-    // 1280x720 of 192^3 F32 1,040 us without and 1,068 with it, 2 x 960x540
-    // with boards 99.5 and 103).
-    constexpr bool lean = DT != DT_F32 && SCENE < 2;
+    // LEAN: a step asks once per wave whether any ray is near a face and once per
+    // ray whether anything ends it, and sorts these out only then.
     uint32_t nh = 0;
     for (int k = 0; k < kRayBins; ++k) nh += *hit_counter(L.counters, k);
     nh = __builtin_amdgcn_readfirstlane(nh);
@@ -995,11 +989,11 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
             if (active) {
                 // ---- one step of Eq. 16 with the step of Eq. 18 ----
                 // Only a step that starts near a face needs the exit distance te
-                // (lean: it is left unset while no lane of the wave is near one).
+                // (LEAN: it is left unset while no lane of the wave is near one).
                 float te;
-                if (lean) asm volatile("" : "=v"(te));
+                if (LEAN) asm volatile("" : "=v"(te));
                 int status = -1, hit_surf = -1;
-                const bool any_near = !lean || __ballot(safe <= S.near_cap) != 0ull;
+                const bool any_near = !LEAN || __ballot(safe <= S.near_cap) != 0ull;
                 if (any_near) {
                     te = INFINITY;
                     if (safe <= S.near_cap) {
@@ -1039,7 +1033,7 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
                     const float pg0 = s.y - wg * w[0], pg1 = s.z - wg * w[1], pg2 = s.w - wg * w[2];
                     float ds;
                     if (S.uniform) {
-                        ds = lean ? in_vgpr(S.ds_uniform) : S.ds_uniform;
+                        ds = LEAN ? in_vgpr(S.ds_uniform) : S.ds_uniform;
                     } else {
                         const float pgn = __builtin_amdgcn_sqrtf(pg0 * pg0 + pg1 * pg1 + pg2 * pg2);
                         // clamp to [ds_min, ds_max] (ds_min <= ds_max, checked on the host) in
@@ -1048,7 +1042,7 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
                                                      K.ds_max);
                     }
                     if (any_near) {   // a branch (the asm keeps it one); in it
-                        if (lean) asm volatile("" : "+v"(te));
+                        if (LEAN) asm volatile("" : "+v"(te));
                         ds = te < ds ? te : ds;   // min(ds, te) as a select: fminf would canonicalize both
                     }
                     // omega_{k+1} = normalize(omega_k + ds/n P g) = normalize(p + |p| ds/n P g)
@@ -1127,7 +1121,7 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
                     // (or p zero); otherwise the step, direction and position stay finite.
                     const bool finite = pn2 > 0.0f && pn2 < INFINITY && fabsf(n) < INFINITY;
                     const bool on = finite && safe > S.pos_eps && (int32_t)steps < S.max_steps;
-                    if (!lean || !on) {
+                    if (!LEAN || !on) {
                         if (!finite)
                             status = 3;
                         else if ((SCENE == 2 || SCENE == 3) && surf >= 0) {
@@ -1159,24 +1153,24 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
 #ifndef HZ_MARCH_F32_WAVES
 #define HZ_MARCH_F32_WAVES 6
 #endif
-template <int DT, int SCENE, bool ONE>
+template <int DT, int SCENE, bool ONE, bool LEAN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DT == DT_F32 ? HZ_MARCH_F32_WAVES : 6)))
 void k_march(TraceLaunch L)
 {
-    march<DT, SCENE, ONE>(L);
+    march<DT, SCENE, ONE, LEAN>(L);
 }
 
 template <int DT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_march_boards(TraceLaunch L)
 {
-    march<DT, 2, false>(L);
+    march<DT, 2, false, false>(L);
 }
 
 template <int DT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_march_mesh(TraceLaunch L)
 {
     load_planes(L.mesh);
-    march<DT, 3, false>(L);
+    march<DT, 3, false, false>(L);
 }
 
 // With a scene in the volume the scene's tests bound a step: the boards' march
@@ -1184,7 +1178,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 template <int SCENE>
 constexpr bool one_field_march = SCENE < 2;
 
-template <int DT, int SCENE, bool ONE>
+// The lean step (see march()) is for marches bound by instruction issue or by one
+// ray's steps: of 16-bit fields (4 x 1920x1080 of 256^3 3,320 us against 3,510)
+// and of F32 fields up to 2^21 slots (4,096 chosen rays 112 against 116, 640x360
+// of 192^3 171 against 178, fixed steps 632 against 658, 2 x 1280x720 423 against
+// 425).  Larger F32 launches are bound by their gathers (8 x 1280x720 1,064
+// against 1,049), and with a scene in the volume its tests count most (boards
+// 103 against 99.5).
+constexpr int64_t kLeanSlots = (int64_t)1 << 21;
+
+template <int DT, int SCENE, bool ONE, bool LEAN>
 static constexpr auto march_kernel()
 {
     if constexpr (SCENE == 2)
@@ -1192,7 +1195,7 @@ static constexpr auto march_kernel()
     else if constexpr (SCENE == 3)
         return &k_march_mesh<DT>;
     else
-        return &k_march<DT, SCENE, ONE>;
+        return &k_march<DT, SCENE, ONE, DT != DT_F32 || LEAN>;
 }
 
 // ---------------------------------------------------------------------------
@@ -1244,15 +1247,27 @@ hipError_t launch_raygen(const TraceLaunch &L, bool clear_counters, hipStream_t 
 
 static int march_scene_mode(const TraceLaunch &L) { return L.mesh.ntris > 0 ? 3 : L.ninner > 0 ? 2 : L.nquads > 0 ? 1 : 0; }
 
+template <int DT, int SCENE, bool ONE, bool LEAN>
+static void launch_march_k(const TraceLaunch &L, int march_blocks, hipStream_t s, const KTimer &t)
+{
+    hipExtLaunchKernelGGL((march_kernel<DT, SCENE, ONE, LEAN>()), dim3(march_blocks), dim3(256),
+                          SCENE == 3 ? mesh_lds(L) : 0, s, t.start, t.stop, 0, L);
+}
+
 template <int DT, int SCENE>
 static void launch_march_t(const TraceLaunch &L, int march_blocks, hipStream_t s, const KTimer &t)
 {
-    if (one_field_march<SCENE> && L.field)
-        hipExtLaunchKernelGGL((march_kernel<DT, SCENE, one_field_march<SCENE>>()), dim3(march_blocks), dim3(256), 0, s,
-                              t.start, t.stop, 0, L);
-    else
-        hipExtLaunchKernelGGL((march_kernel<DT, SCENE, false>()), dim3(march_blocks), dim3(256),
-                              SCENE == 3 ? mesh_lds(L) : 0, s, t.start, t.stop, 0, L);
+    const bool lean = L.nslots <= kLeanSlots;
+    if (one_field_march<SCENE> && L.field) {
+        if (lean)
+            launch_march_k<DT, SCENE, one_field_march<SCENE>, true>(L, march_blocks, s, t);
+        else
+            launch_march_k<DT, SCENE, one_field_march<SCENE>, false>(L, march_blocks, s, t);
+    } else if (lean) {
+        launch_march_k<DT, SCENE, false, true>(L, march_blocks, s, t);
+    } else {
+        launch_march_k<DT, SCENE, false, false>(L, march_blocks, s, t);
+    }
 }
 
 template <int DT>
@@ -1281,10 +1296,10 @@ template <int SCENE>
 static hipError_t occupancy(int dtype, int *nb)
 {
     if (dtype == DT_F32)
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, march_kernel<DT_F32, SCENE, true>(), 256, 0);
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, march_kernel<DT_F32, SCENE, true, false>(), 256, 0);
     if (dtype == DT_F16)
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, march_kernel<DT_F16, SCENE, true>(), 256, 0);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, march_kernel<DT_BF16, SCENE, true>(), 256, 0);
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, march_kernel<DT_F16, SCENE, true, true>(), 256, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, march_kernel<DT_BF16, SCENE, true, true>(), 256, 0);
 }
 
 int march_blocks_per_cu(int dtype, int scene_mode)
