@@ -120,11 +120,12 @@ def test_splat_tiles_parity(ctx, haze, res, h, n, signs):
 
 
 @pytest.mark.parametrize("n,h", [(1, 0.03), (2, 0.2), (63, 0.03), (1023, 0.0268), (1025, 0.03), (4095, 0.0268),
-                                 (4096, 0.0266), (4096, 0.03)])
+                                 (4096, 0.0266), (4096, 0.03), (1, 0.02), (3, 0.02), (5, 0.02), (9, 0.02)])
 def test_small_cell_list_equals_the_large(ctx, haze, n, h):
     """Up to 4,096 particles over 8,192 cells are binned in one launch: the bits
     of the same particles followed by others that are in no cell, which take
-    the general way (h = 0.0268 gives 8,160 cells, 0.0266 8,568)."""
+    the general way (h = 0.0268 gives 8,160 cells, 0.0266 8,568, 0.02 more than
+    14,000: there arrays of less than four slots, or just more, against large)."""
     wl = W.make_small(seed=31, res=(19, 15, 11), h=h, n=max(n, 2))
     p = wl.particles
     x, y, z, m = (np.array(a[:n], np.float32) for a in (p.x, p.y, p.z, p.m))
