@@ -456,7 +456,7 @@ __device__ __forceinline__ uint32_t bin_rank(int bin, uint32_t (*wcnt)[kRayBins]
     uint64_t todo = __ballot(bin < kRayBins);
     while (todo) {
         const int first = (int)__builtin_ctzll(todo);
-        const int b = __builtin_amdgcn_readfirstlane(__shfl(bin, first));
+        const int b = __builtin_amdgcn_readlane(bin, first);
         const uint64_t m = __ballot(bin == b);
         if (lane == 0) wcnt[wave][b] = (uint32_t)__popcll(m);
         if (bin == b)
@@ -583,25 +583,42 @@ __global__ __launch_bounds__(kRaygenBlock) void k_raygen_place(TraceLaunch L)
 {
     const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int bin = slot < L.nslots ? (int)L.slot_bin[slot] : 255;
-    __shared__ uint32_t wcnt[kRaygenBlock / 64][kRayBins];
-    __shared__ uint32_t tot[kRayBins];
-    __shared__ uint32_t base[kRayBins];
+    constexpr int W = kRaygenBlock / 64;
+    __shared__ uint32_t wcnt[W][kRayBins];
+    __shared__ uint4 tot4[kRayBins / 4];
+    uint32_t *const tot = (uint32_t *)tot4;
     if (threadIdx.x < kRayBins) tot[threadIdx.x] = *hit_counter(L.counters, threadIdx.x);
     const uint32_t rank = bin_rank(bin, wcnt);
     __syncthreads();
+    // a thread for each bin: the place of each wave's first ray of the bin
+    // (unrolled, with the counts read at once: every workgroup waits for these
+    // few threads.  8 x 1280x720 29 -> 25 us, 4 x 1920x1080 38 -> 28.5)
     if (threadIdx.x < kRayBins) {
         const int b = threadIdx.x;
-        uint32_t total = 0, start = 0;
-        for (int w = 0; w < kRaygenBlock / 64; ++w) total += wcnt[w][b];
-        for (int k = 0; k < b; ++k) start += tot[k];
-        base[b] = total ? start + atomicAdd(hit_counter(L.counters, kRayBins + b), total) : 0u;
+        uint32_t cnt[W], total = 0, start = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            cnt[w] = wcnt[w][b];
+            total += cnt[w];
+        }
+        if (total) {
+            uint32_t at = atomicAdd(hit_counter(L.counters, kRayBins + b), total);
+#pragma unroll
+            for (int q = 0; q < kRayBins / 4; ++q) {
+                const uint4 v = tot4[q];
+                start += (4 * q < b ? v.x : 0u) + (4 * q + 1 < b ? v.y : 0u) + (4 * q + 2 < b ? v.z : 0u) +
+                         (4 * q + 3 < b ? v.w : 0u);
+            }
+            at += start;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                wcnt[w][b] = at;
+                at += cnt[w];
+            }
+        }
     }
     __syncthreads();
-    if (bin < kRayBins) {
-        uint32_t off = base[bin] + rank;
-        for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) off += wcnt[w][bin];
-        L.hits[off] = (uint32_t)slot;
-    }
+    if (bin < kRayBins) L.hits[wcnt[threadIdx.x >> 6][bin] + rank] = (uint32_t)slot;
 }
 
 __device__ __forceinline__ void wsum(float4 &v, float wgt, const float4 &c)
