@@ -466,18 +466,10 @@ __device__ __forceinline__ uint32_t bin_rank(int bin, uint32_t (*wcnt)[kRayBins]
     return rank;
 }
 
-// The mesh's ray generation holds 104 registers a lane: one workgroup of 1,024 to
-// a compute unit, and 450 of them (2 x 640x360) took two rounds, 53 us against 44
-// in workgroups of 256.  The others: 8 x 1280x720 55.0 us in 1,024, 51.4 in 512,
-// 49.6 in 256, but 4 x 1920x1080 51.4, 49.5 and 65.8 (each workgroup adds to the
-// same counters).
-template <int SCENE>
-constexpr int raygen_block = SCENE == 3 ? 256 : 512;
-
 // SCENE: 0 no scene, 1 boards, 3 triangle mesh (the launch's scene kind, so
 // that the common case carries no scene code).
-template <int SCENE>
-__global__ __launch_bounds__(raygen_block<SCENE>) void k_raygen(TraceLaunch L, const TraceJob *__restrict__ jobs,
+template <int SCENE, int B>
+__global__ __launch_bounds__(B) void k_raygen(TraceLaunch L, const TraceJob *__restrict__ jobs,
                                                                 const SceneQuad *__restrict__ quads)
 {
     if (SCENE == 3) load_planes(L.mesh);
@@ -560,18 +552,18 @@ __global__ __launch_bounds__(raygen_block<SCENE>) void k_raygen(TraceLaunch L, c
         }
     }
     // the next launch's counter set (this launch's march uses the other one)
-    static_assert(kMarchHead < raygen_block<SCENE>, "one workgroup clears a counter set");
+    static_assert(kMarchHead < B, "one workgroup clears a counter set");
     if (blockIdx.x == 0 && threadIdx.x <= kMarchHead) *hit_counter(L.counters_next, threadIdx.x) = 0u;
     // pass 1 of the length sort: remember the bin, count the bins of the
     // workgroup (wave ballots), one atomic per non-empty bin
     if (!enters) bin = 255;
     if (slot < L.nslots) L.slot_bin[slot] = (uint8_t)bin;
-    __shared__ uint32_t wcnt[raygen_block<SCENE> / 64][kRayBins];
+    __shared__ uint32_t wcnt[B / 64][kRayBins];
     bin_rank(bin, wcnt);
     __syncthreads();
     if (threadIdx.x < kRayBins) {
         uint32_t total = 0;
-        for (int w = 0; w < raygen_block<SCENE> / 64; ++w) total += wcnt[w][threadIdx.x];
+        for (int w = 0; w < B / 64; ++w) total += wcnt[w][threadIdx.x];
         if (total) atomicAdd(hit_counter(L.counters, threadIdx.x), total);
     }
 }
@@ -1237,12 +1229,11 @@ hipError_t launch_put_table(void *dst, const void *src, size_t bytes, hipStream_
 // Ray generation for L.nslots > 0 slots; `clear_counters` when the set
 // L.counters was not cleared by the previous launch's ray generation (new
 // memory, or after a failed launch).
-template <int SCENE>
+template <int SCENE, int B>
 static void launch_raygen_t(const TraceLaunch &L, size_t lds, hipStream_t s, hipEvent_t e0)
 {
-    constexpr int B = raygen_block<SCENE>;
-    hipExtLaunchKernelGGL(k_raygen<SCENE>, dim3((unsigned)((L.nslots + B - 1) / B)), dim3(B), lds, s, e0, nullptr, 0, L,
-                          L.jobs, L.quads);
+    hipExtLaunchKernelGGL((k_raygen<SCENE, B>), dim3((unsigned)((L.nslots + B - 1) / B)), dim3(B), lds, s, e0, nullptr,
+                          0, L, L.jobs, L.quads);
 }
 
 hipError_t launch_raygen(const TraceLaunch &L, bool clear_counters, hipStream_t s, const KTimer &t)
@@ -1252,12 +1243,19 @@ hipError_t launch_raygen(const TraceLaunch &L, bool clear_counters, hipStream_t 
         hipExtLaunchKernelGGL(k_trace_init, dim3(1), dim3(64), 0, s, t.start, nullptr, 0, L.counters);
     const dim3 g((unsigned)((L.nslots + kRaygenBlock - 1) / kRaygenBlock));
     hipEvent_t e0 = clear_counters ? nullptr : t.start;
+    // The mesh's ray generation holds 104 registers a lane: one workgroup of 1,024
+    // to a compute unit, and 450 of them (2 x 640x360) took two rounds, 53 us
+    // against 44 in workgroups of 256.  The others run in 512 (2 x 960x540 with
+    // boards 19.5 us in 1,024, 18.8 in 512), but large launches in 1,024: each
+    // workgroup adds to the same counters, and 4 x 1920x1080 rays took 49 us in
+    // 1,024, 49 to 60 in 512 and 66 in 256, by how many of them enter.
+    const bool large = L.nslots > (int64_t)1 << 22;
     if (L.mesh.ntris > 0)
-        launch_raygen_t<3>(L, mesh_lds(L), s, e0);
+        launch_raygen_t<3, 256>(L, mesh_lds(L), s, e0);
     else if (L.nquads > 0)
-        launch_raygen_t<1>(L, 0, s, e0);
+        large ? launch_raygen_t<1, 1024>(L, 0, s, e0) : launch_raygen_t<1, 512>(L, 0, s, e0);
     else
-        launch_raygen_t<0>(L, 0, s, e0);
+        large ? launch_raygen_t<0, 1024>(L, 0, s, e0) : launch_raygen_t<0, 512>(L, 0, s, e0);
     hipExtLaunchKernelGGL(k_raygen_place, g, dim3(kRaygenBlock), 0, s, nullptr, t.stop, 0, L);
     return hipGetLastError();
 }

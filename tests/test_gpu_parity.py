@@ -463,12 +463,12 @@ def test_few_rays_equal_the_full_launch(ctx, haze, n):
 
 
 @pytest.mark.parametrize("dtype,width,height", [("f32", 1021, 700), ("f16", 1021, 600), ("bf16", 1500, 1100),
-                                                ("f32", 1500, 1450)])
+                                                ("f32", 1500, 1450), ("f16", 2300, 1900)])
 def test_second_batches_equal_single_batches(ctx, haze, dtype, width, height):
     """Launches with more rays than their waves hold at once (393,216: the rest
     goes to waves that have finished, reserved late with less than a second
     batch for each) give the bits of launches in which every ray has a lane; so
-    does the F32 step of launches past 2^21 slots."""
+    do the F32 step past 2^21 slots and the ray generation past 2^22."""
     grid = W.make_grid((0.0, 0.0, 0.0), (0.9, 0.8, 1.1), (24, 20, 28))
     rng = np.random.default_rng(2)
     dn = (1e-3 * rng.standard_normal((28, 20, 24))).astype(np.float32)
