@@ -19,7 +19,7 @@
 //   k_raygen_place  places the entering rays in a hit list sorted by bin
 //             (wave ballots + mbcnt ranks, one atomic per workgroup and bin)
 //   k_march   persistent waves pull hit rays from the list in batches of
-//             64; once refill_min lanes have finished (by default all of
+//             64 (fewer where that leaves waves without work); once refill_min lanes have finished (by default all of
 //             them), the idle lanes are refilled together (ballot of idle
 //             lanes, one atomic per batch, mbcnt rank); finished rays write
 //             their outputs at the next refill.  The length sort keeps the
