@@ -462,6 +462,27 @@ def test_few_rays_equal_the_full_launch(ctx, haze, n):
     field.release()
 
 
+@pytest.mark.parametrize("dtype,n,uniform", [("f32", 5, 0), ("f32", 700, 1), ("f32", 20000, 0), ("f16", 700, 0),
+                                             ("f16", 20000, 1), ("bf16", 5, 1), ("bf16", 20000, 0)])
+def test_few_rays_walked_ahead_change_nothing(ctx, haze, dtype, n, uniform):
+    """Launches of few rays have a second wave walk ahead of the march (up to
+    2^17 slots): the bits of the same rays in a launch past that, which has none."""
+    wl = W.make_small(seed=17, width=481, height=333, nviews=1, res=(35, 61, 40))
+    print(f"case {dtype} {n} of {wl.nrays} rays, uniform={uniform}", flush=True)
+    assert wl.nrays > 1 << 17
+    field = ctx.splat_index_field(haze.upload_particles(wl.particles), wl.grid, wl.k_gd * 100.0, wl.h, dtype=dtype,
+                                  store_scale=1.0 if dtype == "f32" else 64.0)
+    step = wl.step_uniform if uniform else wl.step_adaptive
+    full = ctx.trace_views(field, wl.views, step)
+    ids = torch.from_numpy(W.draw_subset(wl.nrays, n, 9)).cuda()
+    sub = ctx.trace_views(field, wl.views, step, ray_ids=ids)
+    assert n < 100 or (sub["steps"] > 1).any()   # (a handful of rays may all miss)
+    for k, v in sub.items():
+        a, b = v.cpu().numpy(), full[k][ids].cpu().numpy()
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), k
+    field.release()
+
+
 @pytest.mark.parametrize("dtype,width,height", [("f32", 1021, 700), ("f16", 1021, 600), ("bf16", 1500, 1100),
                                                 ("f32", 1500, 1450), ("f16", 2300, 1900)])
 def test_second_batches_equal_single_batches(ctx, haze, dtype, width, height):
