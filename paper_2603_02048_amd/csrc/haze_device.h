@@ -51,11 +51,14 @@ struct ScanGuard {
     uint32_t serial;
 };
 
-// Geometry of the tile gather, in units of 2h.
+// Geometry of the tile gather, in units of the power of two that puts 2h in
+// [0.5, 1): scaling by it is exact.
 struct TileGeom {
     double c0[3];    // minus the grid's lower corner
     double sp[3];    // voxel spacing
-    float scale;     // 1 / 2h (c0 and sp are scaled by exactly this float)
+    float scale;     // metres to these units
+    float reach2;    // (2h)^2
+    float ninv;      // -1 / 2h
     float u[3];      // voxel spacing
     float half[3];   // half extents of a block of 4 x 4 x 2 voxel centres, grown by 1e-5
 };

@@ -24,7 +24,7 @@
 namespace haze {
 hipError_t launch_cell_list(const float *, const float *, const float *, const float *, int32_t, const CellGrid &,
                             uint32_t *, uint32_t *, int64_t, uint32_t *, uint32_t *, uint32_t *, float4 *, void *,
-                            bool, uint32_t *, bool, const ScanGuard &, uint32_t *, int32_t, bool, bool, hipStream_t,
+                            bool, uint32_t *, bool, const ScanGuard &, uint32_t *, int32_t, bool, hipStream_t,
                             const KTimer &);
 int32_t scan_tiles(int32_t ncells);
 size_t scan_scratch_bytes(int32_t ncells);
@@ -878,7 +878,11 @@ extern "C" hz_status hz_splat_index_field(hz_ctx *c, const hz_particles *P, cons
     sp.support2 = (float)(4.0 * h * h);
     sp.scale = (float)((double)prm->k_gd / (M_PI * h * h * h));
     sp.cg = cg;
-    sp.tile.scale = (float)(0.5 / h);
+    int two_h_exp;
+    const double reach = std::frexp(2.0 * h, &two_h_exp);
+    sp.tile.scale = (float)std::ldexp(1.0, -two_h_exp);
+    sp.tile.reach2 = (float)(reach * reach);
+    sp.tile.ninv = (float)(-1.0 / reach);
     for (int a = 0; a < 3; ++a) {
         const double scale = (double)sp.tile.scale, spacing = (g->hi[a] - g->lo[a]) / g->res[a];
         sp.tile.c0[a] = -g->lo[a] * scale;
@@ -949,7 +953,7 @@ extern "C" hz_status hz_splat_index_field(hz_ctx *c, const hz_particles *P, cons
     hipError_t e = launch_cell_list(P->x, P->y, P->z, P->m, n, cg, (uint32_t *)c->cid.ptr, (uint32_t *)c->count.ptr,
                                     clear_words, (uint32_t *)c->start.ptr, (uint32_t *)c->lrank.ptr,
                                     (uint32_t *)c->slots.ptr, (float4 *)c->sorted.ptr, c->tiles.ptr, scan_reset,
-                                    &c->scan_base, scatter, guard, bwork, nbricks, ordered, sp.tiles && !scatter, s, t0);
+                                    &c->scan_base, scatter, guard, bwork, nbricks, ordered, s, t0);
     prof_commit(c, "cell_list", t0);
     if (e == hipSuccess) {
         c->count.clean = !scatter;

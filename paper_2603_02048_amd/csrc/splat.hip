@@ -15,9 +15,9 @@
 //   k_cell_scatter particle index -> its slot (cell start + arrival rank from
 //                  the histogram atomics: an arbitrary order inside the cell)
 //   k_cell_order   per particle, its rank by index among its cell's members
-//                  (stable order); (x, y, z, m) into cell-sorted float4 records
-//                  (cbrt(m) for the tile gather); one more workgroup lists the
-//                  column gather's bricks heaviest first (order_bricks_place)
+//                  (stable order); (x, y, z, m) into cell-sorted float4 records;
+//                  one more workgroup lists the column gather's bricks heaviest
+//                  first (order_bricks_place)
 //   k_splat_tiles  tile gather, the usual one: a wave per octant of 4x4x4
 //                  voxels compacts the particles in reach of its blocks of
 //                  4x4x2 in LDS and sums them in tiles of 16 particles x 32
@@ -391,8 +391,7 @@ constexpr int SMALL_CELLS = SMALL_THREADS * SMALL_CELLS_PER_THREAD;
 __global__ __launch_bounds__(SMALL_THREADS) void k_cells_small(const float *__restrict__ x, const float *__restrict__ y,
                                                                const float *__restrict__ z, const float *__restrict__ m,
                                                                int32_t n, CellGrid cg, uint32_t *__restrict__ start,
-                                                               float4 *__restrict__ sorted, uint32_t *__restrict__ fail,
-                                                               int32_t mass_root)
+                                                               float4 *__restrict__ sorted, uint32_t *__restrict__ fail)
 {
     __shared__ uint32_t cell[SMALL_CELLS + 1];   // counts, then starts
     __shared__ uint32_t slots[SMALL_PARTS];
@@ -451,7 +450,6 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_cells_small(const float *__re
         const uint32_t b = cell[id[k]], e = cell[id[k] + 1];
         uint32_t rank = 0u;
         for (uint32_t j = b; j < e; ++j) rank += slots[j] < (uint32_t)(k * SMALL_THREADS + t) ? 1u : 0u;
-        if (mass_root) rec[k].w = (float)cbrt((double)rec[k].w);
         sorted[b + rank] = rec[k];
     }
 }
@@ -482,7 +480,7 @@ __global__ __launch_bounds__(256) void k_cell_order(const uint32_t *__restrict__
                                                     const float *__restrict__ x, const float *__restrict__ y,
                                                     const float *__restrict__ z, const float *__restrict__ m,
                                                     float4 *__restrict__ sorted, const uint32_t *__restrict__ fail,
-                                                    int32_t mass_root, BrickOrder O)
+                                                    BrickOrder O)
 {
     // When ordering the gather's bricks, workgroup 0 places them (the second
     // phase) beside the ordering of the particles (one workgroup later).
@@ -500,9 +498,7 @@ __global__ __launch_bounds__(256) void k_cell_order(const uint32_t *__restrict__
     if (c == 0xffffffffu) return;
     const u32x2 range = *reinterpret_cast<const u32x2 *>(start + c);
     const uint32_t b = range.x, e = range.y;
-    float4 rec = make_float4(x[i], y[i], z[i], m[i]);
-    // the tile gather takes the mass's cube root (rounded once, from double)
-    if (mass_root) rec.w = (float)cbrt((double)rec.w);
+    const float4 rec = make_float4(x[i], y[i], z[i], m[i]);
     // Eight slots per round in two loads (gathers cost the texture-address unit a
     // lane at a time, whatever their width; words of 4 suffice for alignment),
     // from where four are left in the array; entries outside the cell don't count.
@@ -809,23 +805,25 @@ __global__ __launch_bounds__(64 * SPLAT_WAVES) void k_splat(SplatParams P, const
 //      sphere (q < 1) reaches the block and one for the others.
 //   3. Sixteen ring entries form a tile of 16 particles x 32 voxels: a lane
 //      takes one particle (lane & 15) and the eight voxels (k, lane >> 4, g),
-//      whose distances share their differences per axis.  In units of 2h, with
-//      mu the cube root of the particle's mass (stored so by k_cell_order), a
-//      pair costs r = sqrt clamped to 1, w = mu - mu r, w^2 and an FMA:
-//      m t^3 = w^3 (see plane_terms for t and s); the pairs of an inner ring
-//      subtract m s^3 / 2 likewise, from 2r clamped to 1 and mu / cbrt(2).
+//      whose distances share their differences per axis.  A pair costs r =
+//      sqrt, t = 1 - r / 2h clamped at 0, t^2, m t and an FMA (see plane_terms
+//      for t and s); the pairs of an inner ring subtract m s^3 / 2 likewise,
+//      from s = 1 - r / h clamped at 0.  (With the mass's cube root, mu, in the
+//      records (mu - mu r / 2h)^3 takes one operation less, 1,735 us against
+//      1,840 at 256^3; but three octaves of masses then share one of roots, and
+//      up to 1.8e-7 of a mass is lost.)
 // What bounds it is VALU issue.  Measured on the card, in cycles of a SIMD per
 // wave64 instruction: FMA, add, multiply 2.5 as long as other waves can issue
-// beside it (about 4 straight after a square root), square root 8.3; 1,226 M
-// instructions at 256^3, 118 M of them square roots.  So the split aims at few
+// beside it (about 4 straight after a square root), square root 8.3; 1,316 M
+// instructions at 256^3, 116 M of them square roots.  So the split aims at few
 // pair slots and few instructions per slot: blocks of 32 voxels fill 62% of
 // their slots with pairs in reach (the column gather's planes of 8 x 8 voxels
-// 45%), and a slot takes 6.6 instructions.  The squared distances on the
+// 45%), and a slot takes 7.6 instructions.  The squared distances on the
 // matrix cores (v_mfma_f32_16x16x4f32 of (-2v, 1) and (p, |p|^2)) were slower:
 // the FP32 MFMA does not run beside the VALU (8 cycles a slot, against 6 here).
 // Measured, column gather to tiles: 1,048,576 particles on 256^3 voxels 2,060
-// to 1,750 us; 262,144 on 128^3 320 to 245; 16,384 on 64^3 36 to 19; 3,000 on
-// 21x17x13 71 to 12 (here the column gather walks its rows one after another).
+// to 1,840 us; 262,144 on 128^3 320 to 255; 16,384 on 64^3 36 to 19; 3,000 on
+// 21x17x13 71 to 11 (here the column gather walks its rows one after another).
 // Every sum runs in a fixed order (ring order within a lane, then the sixteen
 // lanes, then the waves that share an octant), so the field is bitwise
 // repeatable.
@@ -849,15 +847,15 @@ __device__ __forceinline__ float in_vgpr(float x)
 __device__ __forceinline__ uint64_t lanes_below(uint32_t n) { return n >= 64u ? ~0ull : (1ull << n) - 1ull; }
 
 // The voxels of one lane in a block's tiles: (k, y, g) with k = 0..3, y = lane
-// >> 4, g = 0, 1; coordinates from the octant's centre in units of 2h.
+// >> 4, g = 0, 1; coordinates from the octant's centre (see TileGeom).
 struct TileVoxels {
     float x[4], y, z[2];
 };
 
 // One tile: 16 ring entries against a block's 32 voxels; q is the lane's entry
-// (position, mass root), acc the sums of its eight voxels.
+// (position, mass), acc the sums of its eight voxels, ninv -1 / 2h.
 template <bool INNER>
-__device__ __forceinline__ void tile_terms(const float4 &q, const TileVoxels &V, float acc[2][4])
+__device__ __forceinline__ void tile_terms(const float4 &q, const TileVoxels &V, float ninv, float acc[2][4])
 {
     const float dy = V.y - q.y;
     float dx2[4], r2[2][4];
@@ -872,26 +870,27 @@ __device__ __forceinline__ void tile_terms(const float4 &q, const TileVoxels &V,
 #pragma unroll
         for (int k = 0; k < 4; ++k) r2[g][k] = fmaf(dz, dz, dx2[k]);
     }
-    const float mu = q.w, mi = 0.793700526f * mu;   // mu / cbrt(2)
-    float r[8], w[8], w2[8];
+    const float m = in_vgpr(q.w);   // (read with the position, not behind the roots)
+    float r[8], t[8], t2[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        r[i] = clamp01(__builtin_amdgcn_sqrtf(r2[i >> 2][i & 3]));
-    }
+    for (int i = 0; i < 8; ++i) r[i] = __builtin_amdgcn_sqrtf(r2[i >> 2][i & 3]);
     __builtin_amdgcn_sched_barrier(0);
+    const auto add_cubes = [&](float w) {   // w t^3
 #pragma unroll
-    for (int i = 0; i < 8; ++i) w[i] = fmaf(-r[i], mu, mu);
+        for (int i = 0; i < 8; ++i) t2[i] = t[i] * t[i];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) w2[i] = w[i] * w[i];
+        for (int i = 0; i < 8; ++i) t[i] *= w;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i >> 2][i & 3] = fmaf(w2[i], w[i], acc[i >> 2][i & 3]);
+        for (int i = 0; i < 8; ++i) acc[i >> 2][i & 3] = fmaf(t2[i], t[i], acc[i >> 2][i & 3]);
+    };
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t[i] = clamp01(fmaf(r[i], ninv, 1.0f));
+    add_cubes(m);
     if (INNER) {
+        const float ninv_h = ninv + ninv;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) w[i] = fmaf(-clamp01(r[i] + r[i]), mi, mi);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) w2[i] = -(w[i] * w[i]);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i >> 2][i & 3] = fmaf(w2[i], w[i], acc[i >> 2][i & 3]);
+        for (int i = 0; i < 8; ++i) t[i] = clamp01(fmaf(r[i], ninv_h, 1.0f));
+        add_cubes(-0.5f * m);
     }
 }
 
@@ -910,10 +909,10 @@ __device__ __forceinline__ uint32_t ring_place(const Ring &R, uint64_t mask)
 // Takes the whole tiles of a ring; `q` is this lane's entry of the first tile
 // (entry lane & 15).
 template <bool INNER>
-__device__ __forceinline__ void ring_drain(const float4 *q, Ring &R, const TileVoxels &V, float acc[2][4])
+__device__ __forceinline__ void ring_drain(const float4 *q, Ring &R, const TileVoxels &V, float ninv, float acc[2][4])
 {
     while (R.n >= 16u) {
-        tile_terms<INNER>(q[R.head], V, acc);
+        tile_terms<INNER>(q[R.head], V, ninv, acc);
         R.head += 16u;
         if (R.head >= (uint32_t)TILE_RING) R.head = 0u;
         R.n -= 16u;
@@ -959,9 +958,9 @@ void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const floa
     const int32_t o0[3] = {brick % P.nbx * TILE_BX + 4 * (oct & 1), brick / P.nbx % P.nby * TILE_BY + 4 * (oct >> 1),
                            brick / (P.nbx * P.nby) * TILE_BZ};
     if (o0[0] >= P.res[0] || o0[1] >= P.res[1]) return;   // (the waves of an octant together)
-    // Positions below are from the octant's centre in units of 2h: x = p scale +
-    // c, with c the rounded -(centre) scale; what rounding took from c is taken
-    // off the voxels too.
+    // Positions below are from the octant's centre, scaled (see TileGeom): x =
+    // p scale + c, with c the rounded -(centre) scale; what rounding took from c
+    // is taken off the voxels too.
     const TileGeom &T = P.tile;
     float c[3], e[3], half[3], blo[3], bhi[3];
 #pragma unroll
@@ -985,6 +984,7 @@ void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const floa
 #pragma unroll
         for (int g = 0; g < 2; ++g) vox[zb].z[g] = in_vgpr(fmaf((float)(2 * zb + g) - 1.5f, T.u[2], -e[2]));
     }
+    const float ninv = T.ninv;
     float acc[4][4] = {};
 
     // cell rows that may hold a particle in reach (the slack absorbs rounding:
@@ -1060,7 +1060,7 @@ void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const floa
     const float4 *const mine = my + (lane & 15);
     Ring out0, in0, out1, in1;
     // radii grown by 0.1%: rounding never drops a pair in reach
-    constexpr float RO2 = 1.001f, RI2 = 0.25025f;
+    const float RO2 = 1.001f * T.reach2, RI2 = 0.25f * RO2;
     const auto append = [&](int base, Ring &out, Ring &in, float d2, uint64_t valid, const float4 &rec) {
         const bool near = d2 < RI2;
         const uint64_t hit = __builtin_amdgcn_ballot_w64(d2 < RO2) & valid;
@@ -1076,10 +1076,10 @@ void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const floa
     };
     const auto drain = [&]() {
         wave_lds_fence();
-        ring_drain<false>(mine, out0, vox[0], acc);
-        ring_drain<true>(mine + TILE_RING, in0, vox[0], acc);
-        ring_drain<false>(mine + 2 * TILE_RING, out1, vox[1], acc + 2);
-        ring_drain<true>(mine + 3 * TILE_RING, in1, vox[1], acc + 2);
+        ring_drain<false>(mine, out0, vox[0], ninv, acc);
+        ring_drain<true>(mine + TILE_RING, in0, vox[0], ninv, acc);
+        ring_drain<false>(mine + 2 * TILE_RING, out1, vox[1], ninv, acc + 2);
+        ring_drain<true>(mine + 3 * TILE_RING, in1, vox[1], ninv, acc + 2);
         wave_lds_fence();
     };
     float4 q, q_next;
@@ -1554,7 +1554,7 @@ hipError_t launch_cell_list(const float *x, const float *y, const float *z, cons
                             const CellGrid &cg, uint32_t *cid, uint32_t *count, int64_t count_clear_words,
                             uint32_t *start, uint32_t *lrank, uint32_t *slots, float4 *sorted, void *scan,
                             bool scan_reset, uint32_t *scan_base, bool want_mmax, const ScanGuard &guard,
-                            uint32_t *bwork, int32_t nbricks, bool order, bool mass_root, hipStream_t s, const KTimer &t)
+                            uint32_t *bwork, int32_t nbricks, bool order, hipStream_t s, const KTimer &t)
 {
     // The counts must start at zero; each scan leaves them so.
     // count[ncells+1] holds max |m| (scatter splat only), which the caller
@@ -1582,7 +1582,7 @@ hipError_t launch_cell_list(const float *x, const float *y, const float *z, cons
     }
     if (n <= SMALL_PARTS && cg.ncells <= SMALL_CELLS && !want_mmax && !bwork && guard.tag_bias == 0) {
         hipExtLaunchKernelGGL(k_cells_small, dim3(1), dim3(SMALL_THREADS), 0, s, first ? t.start : nullptr, t.stop, 0, x,
-                              y, z, m, n, cg, start, sorted, fail, mass_root ? 1 : 0);
+                              y, z, m, n, cg, start, sorted, fail);
         return hipGetLastError();
     }
     if (want_mmax)
@@ -1610,7 +1610,7 @@ hipError_t launch_cell_list(const float *x, const float *y, const float *z, cons
     hipLaunchKernelGGL(k_cell_scatter, dim3(blocks_for(n, 256)), dim3(256), 0, s, cid, lrank, n, start, slots,
                        fail);
     hipExtLaunchKernelGGL(k_cell_order, dim3(blocks_for(n, 256) + (O.order ? 1 : 0)), dim3(256), 0, s, nullptr,
-                          t.stop, 0, cid, start, slots, n, x, y, z, m, sorted, fail, mass_root ? 1 : 0, O);
+                          t.stop, 0, cid, start, slots, n, x, y, z, m, sorted, fail, O);
     return hipGetLastError();
 }
 
@@ -1625,9 +1625,9 @@ hipError_t launch_splat(const SplatParams &P, const uint32_t *start, const float
     const dim3 g((unsigned)nbricks), b(64 * SPLAT_WAVES);
     // Up to 256 bricks (1,024 octants, one wave to a SIMD) the launch lasts as
     // long as one octant's particles take a wave: there four waves share them.
-    // One wave / four: 21x17x13 voxels, 3,000 particles 19.0 / 11.7 us; 32^3,
-    // 8,000 15.7 / 12.5; 40^3 (250 bricks), 8,000 19.8 / 16.2; 48^3, 16,384
-    // 19.3 / 22.4; 64^3, 60,000 50 / 61.
+    // One wave / four: 21x17x13 voxels, 3,000 particles 19.4 / 11.8 us; 32^3,
+    // 8,000 15.6 / 11.4; 40^3 (250 bricks), 8,000 20.0 / 15.9; 48^3, 16,384
+    // 19.7 / 22.0; 64^3, 60,000 54 / 66.
     if (P.tiles && nbricks <= 256)
         hipExtLaunchKernelGGL(k_splat_tiles<true>, dim3(4u * (unsigned)nbricks), dim3(256), 0, s, t.start, t.stop, 0, P,
                               start, sorted, nbricks, dn, fail);

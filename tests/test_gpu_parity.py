@@ -119,6 +119,40 @@ def test_splat_tiles_parity(ctx, haze, res, h, n, signs):
     again.release()
 
 
+@pytest.mark.parametrize("brick_z", [0, 4, 8])
+@pytest.mark.parametrize("side", [15, 40, 60])
+def test_splat_holds_masses_in_full(ctx, haze, side, brick_z):
+    """delta-n is linear in a particle's mass to a rounding of the product.
+    Particles on voxel centres five voxels apart, h of one voxel: at such a voxel
+    t = s = 1, at its neighbours t = 1/2 and s = 0 exactly, so that every term
+    but the product with the scale is exact, whatever the mass (tolerance: 2^-23
+    of the value, twice that product's rounding)."""
+    grid = W.make_grid((0.0, 0.0, 0.0), (side,) * 3, (side,) * 3)
+    c = np.arange(2, side, 5)
+    at = np.stack(np.meshgrid(c, c, c, indexing="ij"), -1).reshape(-1, 3)
+    rng = np.random.default_rng(23)
+    n = len(at)
+
+    def splat(m):
+        parts = W.Particles(*((at[:, a] + 0.5).astype(np.float32) for a in range(3)), m=m.astype(np.float32))
+        f = ctx.splat_index_field(haze.upload_particles(parts), grid, 2.26e-4, 1.0)
+        dn = ctx.field_read(f)[0].cpu().numpy().astype(np.float64)
+        f.release()
+        x, y, z = at.T
+        return np.concatenate([dn[z, y, x], dn[z, y, x + 1], dn[z, y - 1, x], dn[z + 1, y, x]])
+
+    print(f"case masses {side}^3 brick_z={brick_z}: {n} particles", flush=True)
+    ctx.tune("splat.brick_z", brick_z)
+    try:
+        one = splat(np.ones(n))
+        assert np.all(one > 0.0) and len(np.unique(one)) == 2
+        for m in (rng.uniform(1.0, 8.0, n), 10.0 ** rng.uniform(-9.0, 9.0, n) * rng.choice([-1.0, 1.0], n)):
+            ref = one * np.tile(m.astype(np.float32).astype(np.float64), 4)
+            assert np.max(np.abs(splat(m) / ref - 1.0)) <= 2.0 ** -23
+    finally:
+        _default(ctx)
+
+
 @pytest.mark.parametrize("n,h", [(1, 0.03), (2, 0.2), (63, 0.03), (1023, 0.0268), (1025, 0.03), (4095, 0.0268),
                                  (4096, 0.0266), (4096, 0.03), (1, 0.02), (3, 0.02), (5, 0.02), (9, 0.02)])
 def test_small_cell_list_equals_the_large(ctx, haze, n, h):
