@@ -859,17 +859,22 @@ extern "C" hz_status hz_splat_index_field(hz_ctx *c, const hz_particles *P, cons
         sp.bz = c->splat_brick_z;
     else
         sp.bz = (double)sp.sp[2] <= 2.82842712 * 0.5 * ((double)sp.sp[0] + (double)sp.sp[1]) ? 8 : 4;
-    // The tile gather, unless a brick depth of the column gather is asked for,
-    // or a large fine grid holds few particles: there a wave of the tile
-    // gather has little to do per octant, and the column gather's larger
-    // bricks are faster.  Cell list and splat, tile / column, at 160^3 voxels:
-    // support of 10 voxels, 35 neighbours 161 / 155 us, 70 neighbours 207 / 212;
-    // support of 8 voxels, 35 neighbours 163 / 167; 256^3, support of 10 voxels,
-    // 27 neighbours 545 / 492.
+    // The tile gather, unless a brick depth of the column gather is asked for, or
+    // a large fine grid holds few particles: there a wave of the tile gather has
+    // little to do per octant, and the column gather's larger bricks are faster
+    // (with hardly any particles the tile gather's shorter way to none again).
+    // Cell list and splat in us, tile / column, by grid, support in voxels and
+    // particles within the support: 160^3 and 10 voxels, 10 particles 120 / 133, 20
+    // 150 / 137, 50 189 / 176, 100 253 / 263; 12 voxels, 50 176 / 161, 100 235 /
+    // 231; 8 voxels, 20 147 / 141, 50 197 / 199; 256^3 and 12 voxels, 50 662 / 571;
+    // 128^3 and 10 voxels, 50 108 / 105; 100^3 and 10 voxels, 40 61 / 71.  (Few
+    // particles besides: the one-launch cell list, which does not order bricks,
+    // saves the tile gather 11 us.)
     const double cellv = (double)sp.sp[0] * sp.sp[1] * sp.sp[2], ball = 4.0 / 3.0 * M_PI * 8.0 * h * h * h;
     const double nvox = (double)g->res[0] * g->res[1] * g->res[2];
-    const bool sparse = nvox >= (double)(1 << 21) && ball >= 4.0 / 3.0 * M_PI * 729.0 * cellv &&
-                        (double)P->n * ball < 50.0 * cellv * nvox;
+    const double near = (double)P->n * ball / (cellv * nvox);               // particles within the support
+    const double reach_vox = std::cbrt(ball / cellv / (4.0 / 3.0 * M_PI));   // support in voxels
+    const bool sparse = nvox >= 1.5e6 && P->n > 3000 && near >= 14.0 && near < 14.0 * reach_vox - 64.0;
     sp.tiles = c->splat_brick_z == 0 && !sparse;
     if (sp.tiles) sp.bz = 4;
     sp.nbz = (g->res[2] + sp.bz - 1) / sp.bz;

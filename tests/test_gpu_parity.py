@@ -153,6 +153,37 @@ def test_splat_holds_masses_in_full(ctx, haze, side, brick_z):
         _default(ctx)
 
 
+@pytest.mark.parametrize("side,reach,near,column", [(128, 12, 70, True), (128, 12, 110, False), (128, 12, 12, False),
+                                                    (115, 10, 40, True), (114, 10, 40, False), (115, 7, 36, False),
+                                                    (128, 20, 45, False), (128, 20, 50, True)])
+def test_sparse_fields_take_the_column_gather(ctx, haze, side, reach, near, column):
+    """A large grid with a support of many voxels and few particles in it takes
+    the column gather by default: the bits of brick_z = 8, and past each side of
+    the rule (grid size, support in voxels, particles within it, particles in
+    all) those of the tile gather, which are others.  Both match the oracle, in
+    one context that alternates between them."""
+    h = 0.5 * reach / side
+    n = int(near / (4.0 / 3.0 * np.pi * (2.0 * h) ** 3))
+    rng = np.random.default_rng(29)
+    parts = W.plume_particles(rng, n, (0.0, 0.0, 0.0), (1.0, 1.0, 1.0), [(0.5, 0.5, 60.0, 0.1)])
+    wl = W.Workload("sparse", parts, W.make_grid((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), (side,) * 3), 2.26e-4, h, [], None,
+                    None)
+    field, md = _splat_both(ctx, haze, wl)
+    out = _field_np(ctx, field)
+    field.release()
+    assert_field_match(out[0], out[1:], md.arrays[0], md.arrays[1:], wl.grid.spacing, f"sparse {side} {reach} {near}")
+    ctx.tune("splat.brick_z", 8)
+    try:
+        field = ctx.splat_index_field(haze.upload_particles(parts), wl.grid, wl.k_gd, h)
+        forced = _field_np(ctx, field)
+        field.release()
+    finally:
+        _default(ctx)
+    same = all(np.array_equal(a.view(np.uint32), b.view(np.uint32)) for a, b in zip(out, forced))
+    assert same == column
+    assert_field_match(forced[0], forced[1:], md.arrays[0], md.arrays[1:], wl.grid.spacing, "column gather")
+
+
 @pytest.mark.parametrize("n,h", [(1, 0.03), (2, 0.2), (63, 0.03), (1023, 0.0268), (1025, 0.03), (4095, 0.0268),
                                  (4096, 0.0266), (4096, 0.03), (1, 0.02), (3, 0.02), (5, 0.02), (9, 0.02)])
 def test_small_cell_list_equals_the_large(ctx, haze, n, h):
