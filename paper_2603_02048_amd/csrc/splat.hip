@@ -1479,27 +1479,31 @@ __global__ __launch_bounds__(GPX_T * GPX_T) void k_grad_pack_xyz(const float *__
     }
 }
 
-// Packed (z-fast) field -> [z][y][x] arrays.  A workgroup takes 32 (x) x 16 (z)
-// voxels of one y, read along z and written along x through LDS: 256 (F32) or
-// 128 contiguous bytes a read, 128 a write.  One thread per output voxel,
-// reading across z-columns, took 192 us for a 256^3 F32 field; this 106 us
-// (537 MB: 106 us at the rate of a copy); 193x150x111 BF16 46 to 22 us.
-constexpr int UP_X = 32, UP_Z = 16;
-
-template <int DT>
-__global__ __launch_bounds__(256) void k_field_unpack(const void *__restrict__ in, int32_t rx, int32_t ry,
-                                                      int32_t rz, float inv_scale, float *__restrict__ dn,
+// Packed (z-fast) field -> [z][y][x] arrays: a transpose of rx ry columns by rz
+// planes, whatever rx and ry (a column's number j rx + i is its place in a plane
+// of the arrays too).  A workgroup takes 512 voxels, 32 columns by 16 planes, or
+// more columns of a field with fewer planes, reads them along z and writes them
+// along the columns through LDS: 256 (F32) or 128 contiguous bytes a read, 128 a
+// write.  One thread per output voxel, reading across z-columns, took 192 us for
+// a 256^3 F32 field; this 106 us (537 MB: 106 us at the rate of a copy).
+// 193x150x111 BF16 46 to 25 us (with the call); in tiles of 32 x 16 (x, z) with
+// one y a thin field left most lanes idle: 2x4096x4096 F32 1,960 to 221 us (one
+// thread per voxel 476), 4096x4096x2 463 to 190 (277).
+template <int DT, int Z>
+__global__ __launch_bounds__(256) void k_field_unpack(const void *__restrict__ in, uint32_t columns, uint32_t planes,
+                                                      uint32_t zblocks, float inv_scale, float *__restrict__ dn,
                                                       float *__restrict__ gx, float *__restrict__ gy,
                                                       float *__restrict__ gz)
 {
-    __shared__ float tile[4][UP_Z][UP_X + 1];
-    const int32_t k0 = (int32_t)blockIdx.x * UP_Z, i0 = (int32_t)blockIdx.y * UP_X, j = (int32_t)blockIdx.z;
+    constexpr uint32_t C = 512 / Z;
+    __shared__ float tile[4][Z][C + 1];
+    const uint32_t k0 = blockIdx.x % zblocks * Z, c0 = blockIdx.x / zblocks * C;
 #pragma unroll
-    for (int t = 0; t < UP_X * UP_Z; t += 256) {
-        const int z = (t + (int)threadIdx.x) % UP_Z, x = (t + (int)threadIdx.x) / UP_Z;
-        const int32_t k = k0 + z, i = i0 + x;
-        if (k >= rz || i >= rx) continue;
-        const int64_t w = ((int64_t)j * rx + i) * rz + k;
+    for (uint32_t t = 0; t < 512u; t += 256u) {
+        const uint32_t z = (t + threadIdx.x) % Z, x = (t + threadIdx.x) / Z;
+        const uint32_t k = k0 + z, c = c0 + x;
+        if (k >= planes || c >= columns) continue;
+        const size_t w = (size_t)c * planes + k;
         float4 f;
         if (DT == DT_F32) {
             f = reinterpret_cast<const float4 *>(in)[w];
@@ -1524,11 +1528,11 @@ __global__ __launch_bounds__(256) void k_field_unpack(const void *__restrict__ i
     }
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < UP_X * UP_Z; t += 256) {
-        const int x = (t + (int)threadIdx.x) % UP_X, z = (t + (int)threadIdx.x) / UP_X;
-        const int32_t k = k0 + z, i = i0 + x;
-        if (k >= rz || i >= rx) continue;
-        const int64_t v = ((int64_t)k * ry + j) * rx + i;
+    for (uint32_t t = 0; t < 512u; t += 256u) {
+        const uint32_t x = (t + threadIdx.x) % C, z = (t + threadIdx.x) / C;
+        const uint32_t k = k0 + z, c = c0 + x;
+        if (k >= planes || c >= columns) continue;
+        const size_t v = (size_t)k * columns + c;
         if (dn) dn[v] = tile[0][z][x];
         if (gx) gx[v] = tile[1][z][x];
         if (gy) gy[v] = tile[2][z][x];
@@ -1680,18 +1684,40 @@ hipError_t launch_grad_pack(int dtype, const float *dn, bool dn_zfast, const int
     return hipGetLastError();
 }
 
+template <int DT, int Z>
+static void launch_field_unpack_t(const void *in, const int32_t r[3], float inv_scale, float *dn, float *gx, float *gy,
+                                  float *gz, hipStream_t s)
+{
+    const uint32_t columns = (uint32_t)r[0] * (uint32_t)r[1], planes = (uint32_t)r[2], zblocks = (planes + Z - 1) / Z;
+    // (fields hold fewer than 2^31 voxels: about 2^23 workgroups at most)
+    const uint32_t blocks = zblocks * ((columns + 512 / Z - 1) / (512 / Z));
+    hipLaunchKernelGGL((k_field_unpack<DT, Z>), dim3(blocks), dim3(256), 0, s, in, columns, planes, zblocks, inv_scale,
+                       dn, gx, gy, gz);
+}
+
+template <int DT>
+static void launch_field_unpack_z(const void *in, const int32_t r[3], float inv_scale, float *dn, float *gx, float *gy,
+                                  float *gz, hipStream_t s)
+{
+    if (r[2] <= 2)
+        launch_field_unpack_t<DT, 2>(in, r, inv_scale, dn, gx, gy, gz, s);
+    else if (r[2] <= 4)
+        launch_field_unpack_t<DT, 4>(in, r, inv_scale, dn, gx, gy, gz, s);
+    else if (r[2] <= 8)
+        launch_field_unpack_t<DT, 8>(in, r, inv_scale, dn, gx, gy, gz, s);
+    else
+        launch_field_unpack_t<DT, 16>(in, r, inv_scale, dn, gx, gy, gz, s);
+}
+
 hipError_t launch_field_unpack(int dtype, const void *in, const int32_t res[3], float inv_scale, float *dn, float *gx,
                                float *gy, float *gz, hipStream_t s)
 {
-    const dim3 g((unsigned)((res[2] + UP_Z - 1) / UP_Z), (unsigned)((res[0] + UP_X - 1) / UP_X), (unsigned)res[1]);
-    const dim3 b(256);
     if (dtype == DT_F32)
-        hipLaunchKernelGGL(k_field_unpack<DT_F32>, g, b, 0, s, in, res[0], res[1], res[2], inv_scale, dn, gx, gy, gz);
+        launch_field_unpack_z<DT_F32>(in, res, inv_scale, dn, gx, gy, gz, s);
     else if (dtype == DT_F16)
-        hipLaunchKernelGGL(k_field_unpack<DT_F16>, g, b, 0, s, in, res[0], res[1], res[2], inv_scale, dn, gx, gy, gz);
+        launch_field_unpack_z<DT_F16>(in, res, inv_scale, dn, gx, gy, gz, s);
     else
-        hipLaunchKernelGGL(k_field_unpack<DT_BF16>, g, b, 0, s, in, res[0], res[1], res[2], inv_scale, dn, gx, gy,
-                           gz);
+        launch_field_unpack_z<DT_BF16>(in, res, inv_scale, dn, gx, gy, gz, s);
     return hipGetLastError();
 }
 

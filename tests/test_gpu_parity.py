@@ -511,6 +511,38 @@ def test_grid_import_and_read_back(ctx, haze, res, dtype):
     field.release()
 
 
+@pytest.mark.parametrize("res", [(9, 29, 2), (2, 130, 3), (3, 43, 4), (64, 2, 5), (11, 23, 8), (7, 19, 9), (2, 2, 17)])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_thin_fields_read_back(ctx, haze, res, dtype):
+    """Fields of few planes are read back in tiles of 256, 128, 64 or 32 columns."""
+    test_grid_import_and_read_back(ctx, haze, res, dtype)
+
+
+def _fastest(f, reps=8):
+    out = []
+    for _ in range(reps):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        out.append(a.elapsed_time(b))
+    return min(out[2:])
+
+
+def test_read_back_takes_thin_fields_as_fast(ctx, haze):
+    """Reading back 2^25 voxels is bound by memory whichever axis holds two of
+    them (within a factor of 1.6: lanes idle by the shape cost 2 to 9)."""
+    t = {}
+    for res in ((4096, 2, 4096), (2, 4096, 4096), (4096, 4096, 2)):
+        dn = torch.rand(res[::-1], device="cuda")
+        field = ctx.index_field_from_grid(dn, W.make_grid((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), res))
+        t[res] = _fastest(lambda: ctx.field_read(field))
+        field.release()
+    print(f"case thin read-back: {t}", flush=True)
+    assert max(t.values()) < 1.6 * t[(4096, 2, 4096)]
+
+
 @pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 64, 65, 1024, 4095, 4097, 16389, 40000])
 def test_few_rays_equal_the_full_launch(ctx, haze, n):
     """The march deals few rays in smaller batches: whatever the batch, a ray's
