@@ -1411,16 +1411,16 @@ __global__ __launch_bounds__(256) void k_grad_pack(const float *__restrict__ dn,
 // take 41 us (201 MB: 40 us at the rate of a copy), to F32 90 us; read along z,
 // 4 useful bytes per lane and line, they took 192 and 224.  193x150x111 to
 // BF16: 39 to 16 us.
-constexpr int GPX_T = 16;
-
-template <int DT>
-__global__ __launch_bounds__(GPX_T * GPX_T) void k_grad_pack_xyz(const float *__restrict__ dn, int32_t rx, int32_t ry,
+// A field of up to four voxels along x takes tiles of 4 x 64 (x, z):
+// 2x512x512 F32 8.2 to 6.5 us (read along z 7.5), 2x4096x4096 430 to 288 (737).
+template <int DT, int X>
+__global__ __launch_bounds__(256) void k_grad_pack_xyz(const float *__restrict__ dn, int32_t rx, int32_t ry,
                                                                  int32_t rz, float ix, float iy, float iz,
                                                                  float scale, int32_t planes, void *__restrict__ out)
 {
-    constexpr int HALO = GPX_T + 2, CELLS = HALO * HALO, PER = (CELLS + GPX_T * GPX_T - 1) / (GPX_T * GPX_T);
-    __shared__ float plane[3][HALO][HALO + 1];   // [z][x], with one neighbour on either side
-    const int32_t k0 = (int32_t)blockIdx.x * GPX_T, i0 = (int32_t)blockIdx.y * GPX_T, j0 = (int32_t)blockIdx.z * planes;
+    constexpr int Z = 256 / X, HX = X + 2, CELLS = HX * (Z + 2), PER = (CELLS + 255) / 256;
+    __shared__ float plane[3][Z + 2][HX + 1];   // [z][x], with one neighbour on either side
+    const int32_t k0 = (int32_t)blockIdx.x * Z, i0 = (int32_t)blockIdx.y * X, j0 = (int32_t)blockIdx.z * planes;
     const int32_t j1 = min(j0 + planes, ry);
     // this thread's share of a plane: read along x, kept in registers until
     // the plane's turn (neighbours beyond the grid repeat the face, whose
@@ -1429,8 +1429,8 @@ __global__ __launch_bounds__(GPX_T * GPX_T) void k_grad_pack_xyz(const float *__
     float ahead[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const int t = min((int)threadIdx.x + u * GPX_T * GPX_T, CELLS - 1);
-        const int z = t / HALO, x = t - z * HALO;
+        const int t = min((int)threadIdx.x + u * 256, CELLS - 1);
+        const int z = t / HX, x = t - z * HX;
         const int32_t k = min(max(k0 + z - 1, 0), rz - 1), i = min(max(i0 + x - 1, 0), rx - 1);
         src[u] = dn + ((int64_t)k * ry + j0) * rx + i;
     }
@@ -1444,12 +1444,12 @@ __global__ __launch_bounds__(GPX_T * GPX_T) void k_grad_pack_xyz(const float *__
     const auto put = [&](int b) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            const int t = min((int)threadIdx.x + u * GPX_T * GPX_T, CELLS - 1);
-            plane[b][t / HALO][t % HALO] = ahead[u];
+            const int t = min((int)threadIdx.x + u * 256, CELLS - 1);
+            plane[b][t / HX][t % HX] = ahead[u];
         }
     };
     // this thread's voxels: z fastest
-    const int z = (int)threadIdx.x & (GPX_T - 1), x = (int)threadIdx.x / GPX_T;
+    const int z = (int)threadIdx.x % Z, x = (int)threadIdx.x / Z;
     const int32_t k = k0 + z, i = i0 + x;
     const bool mine = k < rz && i < rx;
     float ym = mine && j0 > 0 ? dn[((int64_t)k * ry + j0 - 1) * rx + i] : 0.0f;
@@ -1647,6 +1647,21 @@ hipError_t launch_splat(const SplatParams &P, const uint32_t *start, const float
     return hipGetLastError();
 }
 
+template <int DT, int X>
+static void launch_grad_pack_xyz(const float *dn, const int32_t r[3], const float inv[3], float scale, void *out,
+                                 hipStream_t s, const KTimer &t)
+{
+    // Planes per workgroup: 8, as long as that leaves 1,024 workgroups, then
+    // 4 or 2.  With 8, 4 and 2 planes: 256^3 to F32 90, 98, 109 us; 64^3,
+    // where 8 planes leave 128 workgroups, 6.2, 5.0, 4.7.
+    const unsigned gz = (unsigned)((r[2] + 256 / X - 1) / (256 / X)), gx = (unsigned)((r[0] + X - 1) / X);
+    int32_t planes = 8;
+    while (planes > 2 && (int64_t)gz * gx * ((r[1] + planes - 1) / planes) < 1024) planes >>= 1;
+    // (each axis has at most 65,535 voxels, so the grid's y and z fit)
+    hipExtLaunchKernelGGL((k_grad_pack_xyz<DT, X>), dim3(gz, gx, (unsigned)((r[1] + planes - 1) / planes)), dim3(256), 0,
+                          s, t.start, t.stop, 0, dn, r[0], r[1], r[2], inv[0], inv[1], inv[2], scale, planes, out);
+}
+
 template <int DT>
 static void launch_grad_pack_t(const float *dn, bool dn_zfast, const int32_t r[3], const float inv[3], float scale,
                                void *out, hipStream_t s, const KTimer &t)
@@ -1656,17 +1671,10 @@ static void launch_grad_pack_t(const float *dn, bool dn_zfast, const int32_t r[3
         const int32_t nblocks = gz * gx * gy, per_xcd = (nblocks + 7) / 8;
         hipExtLaunchKernelGGL(k_grad_pack<DT>, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, s, t.start, t.stop, 0, dn,
                               r[0], r[1], r[2], inv[0], inv[1], inv[2], scale, gz, gx, nblocks, per_xcd, out);
+    } else if (r[0] <= 4) {
+        launch_grad_pack_xyz<DT, 4>(dn, r, inv, scale, out, s, t);
     } else {
-        // Planes per workgroup: 8, as long as that leaves 1,024 workgroups, then
-        // 4 or 2.  With 8, 4 and 2 planes: 256^3 to F32 90, 98, 109 us; 64^3,
-        // where 8 planes leave 128 workgroups, 6.2, 5.0, 4.7.
-        const unsigned gz = (unsigned)((r[2] + GPX_T - 1) / GPX_T), gx = (unsigned)((r[0] + GPX_T - 1) / GPX_T);
-        int32_t planes = 8;
-        while (planes > 2 && (int64_t)gz * gx * ((r[1] + planes - 1) / planes) < 1024) planes >>= 1;
-        // (each axis has at most 65,535 voxels, so the grid's y and z fit)
-        hipExtLaunchKernelGGL(k_grad_pack_xyz<DT>, dim3(gz, gx, (unsigned)((r[1] + planes - 1) / planes)),
-                              dim3(GPX_T * GPX_T), 0, s, t.start, t.stop, 0, dn, r[0], r[1], r[2], inv[0], inv[1],
-                              inv[2], scale, planes, out);
+        launch_grad_pack_xyz<DT, 16>(dn, r, inv, scale, out, s, t);
     }
 }
 

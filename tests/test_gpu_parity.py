@@ -543,6 +543,25 @@ def test_read_back_takes_thin_fields_as_fast(ctx, haze):
     assert max(t.values()) < 1.6 * t[(4096, 2, 4096)]
 
 
+@pytest.mark.parametrize("res", [(2, 2, 63), (2, 9, 64), (3, 10, 65), (4, 17, 129), (5, 17, 129)])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_narrow_grids_import(ctx, haze, res, dtype):
+    """Grids of up to four voxels along x are packed in tiles of 4 x 64 (x, z)."""
+    test_grid_import_and_read_back(ctx, haze, res, dtype)
+
+
+def test_import_takes_narrow_grids_as_fast(ctx, haze):
+    """Packing 2^25 voxels of a grid two voxels wide stays within a factor of 1.7
+    of one two voxels deep (2 and more with most lanes idle)."""
+    t = {}
+    for res in ((4096, 2, 4096), (2, 4096, 4096)):
+        dn = torch.rand(res[::-1], device="cuda")
+        grid = W.make_grid((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), res)
+        t[res] = _fastest(lambda: ctx.index_field_from_grid(dn, grid).release(), 20)
+    print(f"case narrow import: {t}", flush=True)
+    assert t[(2, 4096, 4096)] < 1.7 * t[(4096, 2, 4096)]
+
+
 @pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 64, 65, 1024, 4095, 4097, 16389, 40000])
 def test_few_rays_equal_the_full_launch(ctx, haze, n):
     """The march deals few rays in smaller batches: whatever the batch, a ray's
