@@ -621,9 +621,15 @@ __device__ __forceinline__ void wsum(float4 &v, float wgt, const float4 &c)
     v.w = fmaf(wgt, c.w, v.w);
 }
 
-// Grid constants of the march in vector registers: an FMA, add or multiply
-// with a scalar-register operand takes the slower of the two issue paths (4.4
-// against 2.5 cycles of a SIMD measured), and two scalar operands cost a move.
+// Grid constants of the march, those of 16-bit float fields in vector registers:
+// an FMA, add or multiply with a scalar-register operand takes the slower of the
+// two issue paths (4.4 against 2.5 cycles of a SIMD measured), and two scalar
+// operands cost a move.  All of them where there is room, with the rows' bases in
+// scalar registers (see FieldRows) or a register budget of five waves (boards,
+// 2 x 960x540: 89.7 us with none, 87.5); with an address per view and row the
+// offsets only (nine requests over four 256^3 F16 fields 3,993 us with none, 3,907
+// with the offsets; with all 3,900, but 21 registers spilled, and chosen rays of
+// such a launch, 700,000 of two views, 1,806 us against 1,657); none with a mesh.
 struct MarchConst {
     float inv_sp[3], off[3];
     float magic;       // 2^23
@@ -637,15 +643,15 @@ __device__ __forceinline__ float in_vgpr(float x)
     return x;
 }
 
-template <int DT>
+template <bool ALL, bool OFF>
 __device__ __forceinline__ MarchConst march_const(const TraceGrid &G, const TraceStep &S)
 {
-    const auto put = [](float x) { return DT == DT_F16 ? in_vgpr(x) : x; };
+    const auto put = [](float x) { return ALL ? in_vgpr(x) : x; };
     MarchConst K;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         K.inv_sp[a] = put(G.inv_sp[a]);
-        K.off[a] = put(G.off[a]);
+        K.off[a] = OFF ? in_vgpr(G.off[a]) : G.off[a];
     }
     K.magic = put(8388608.0f);
     K.inv_scale = put(G.inv_scale);
@@ -914,7 +920,7 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
 {
     const TraceGrid &G = L.grid;
     const TraceStep &S = L.step;
-    const MarchConst K = march_const<DT>(G, S);
+    const MarchConst K = march_const<DT == DT_F16 && (ONE || SCENE == 2), DT == DT_F16 && SCENE != 3>(G, S);
     const FieldRows rows = ONE ? field_rows<DT>(G, L.field) : FieldRows{};
     constexpr bool LEAN = STEP != kStepPlain;
     // LEAN: a step asks once per wave whether any ray is near a face and once per
