@@ -1317,13 +1317,16 @@ hipError_t launch_raygen(const TraceLaunch &L, bool clear_counters, hipStream_t 
         hipExtLaunchKernelGGL(k_trace_init, dim3(1), dim3(64), 0, s, t.start, nullptr, 0, L.counters);
     const dim3 g((unsigned)((L.nslots + kRaygenBlock - 1) / kRaygenBlock));
     hipEvent_t e0 = clear_counters ? nullptr : t.start;
-    // The mesh's ray generation holds 104 registers a lane: one workgroup of 1,024
+    // The mesh's ray generation holds 76 registers a lane: one workgroup of 1,024
     // to a compute unit, and 450 of them (2 x 640x360) took two rounds, 53 us
     // against 44 in workgroups of 256.  The others run in 512 (2 x 960x540 with
     // boards 19.5 us in 1,024, 18.8 in 512), but large launches in 1,024: each
-    // workgroup adds to the same counters, and 4 x 1920x1080 rays took 49 us in
-    // 1,024, 49 to 60 in 512 and 66 in 256, by how many of them enter.
-    const bool large = L.nslots > (int64_t)1 << 22;
+    // workgroup adds to the same counters, once for each bin among its entering
+    // rays.  1,024 / 512: 1280x720 18.2 / 16.3 us when a third enters and 22.0 /
+    // 24.4 when all do, 1920x1080 27.4 / 24.4 and 31.7 / 41.0.  Chosen rays enter
+    // all and lie in many bins: 100,000 of them 13.6 / 12.6 us, 200,000 15.9 / 16.0,
+    // 400,000 20.9 / 24.4, 2,500,000 72 / 92.
+    const bool large = L.nslots > (int64_t)1 << (L.subset ? 18 : 20);
     if (L.mesh.ntris > 0)
         launch_raygen_t<3, 256>(L, mesh_lds(L), s, e0);
     else if (L.nquads > 0)
