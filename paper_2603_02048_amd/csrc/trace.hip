@@ -1260,12 +1260,12 @@ constexpr bool one_field_march = SCENE < 2;
 
 // The lean step (see march()) is for marches bound by instruction issue or by one
 // ray's steps: of 16-bit fields (4 x 1920x1080 of 256^3 3,320 us against 3,510)
-// and of F32 fields up to 2^21 slots (4,096 chosen rays 112 against 116, 640x360
-// of 192^3 171 against 178, fixed steps 632 against 658, 2 x 1280x720 423 against
-// 425).  Larger F32 launches are bound by their gathers (8 x 1280x720 1,064
-// against 1,049), and with a scene in the volume its tests count most (boards
-// 103 against 99.5).
-constexpr int64_t kLeanSlots = (int64_t)1 << 21;
+// and of F32 fields up to 2^20 slots (4,096 chosen rays 112 against 116, 640x360
+// of 128^3 171 against 178, fixed steps 632 against 658).  Larger F32 launches may
+// be bound by their gathers (1920x1080 with 1.4 M rays entering 807 against 788,
+// with 0.55 M 336 and 337, 2 x 1280x720 with every ray entering 967 and 950), and
+// with a scene in the volume its tests count most (boards 103 against 99.5).
+constexpr int64_t kLeanSlots = (int64_t)1 << 20;
 // The walk ahead is for launches of at most 32,768 entering rays; larger ones don't
 // carry its code (640x360 of 192^3, 76,800 rays, 171 us without and 175 with it).
 constexpr int64_t kWalkSlots = (int64_t)1 << 17;
