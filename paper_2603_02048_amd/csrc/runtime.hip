@@ -43,7 +43,8 @@ hipError_t launch_field_unpack(int, const void *, const int32_t[3], float, float
 hipError_t launch_raygen(const TraceLaunch &, bool, hipStream_t, const KTimer &);
 hipError_t launch_march(int, const TraceLaunch &, int, hipStream_t, const KTimer &);
 hipError_t launch_put_table(void *dst, const void *src, size_t bytes, hipStream_t s);
-int march_blocks_per_cu(int, int);
+int march_blocks_per_cu(int, int, bool);
+bool march_large(int64_t);
 const MeshLaunch &mesh_launch(const hz_mesh *m);
 float mesh_reach(const hz_mesh *m);
 hz_ctx *mesh_ctx(const hz_mesh *m);
@@ -144,8 +145,7 @@ struct hz_ctx {
     hipEvent_t marks[kMarkRing] = {};
     uint64_t mark_next = 1;
     std::mutex mark_mu;
-    int march_bpc[3] = {0, 0, 0};          // by dtype, no scene boards
-    int march_bpc_scene[3][3] = {};      // by scene mode (outer boards / inner boards / mesh) and dtype
+    int march_bpc[2][4][3] = {};   // large launch or not, scene mode (none, outer boards, inner boards, mesh), dtype
     // march tuning (hz_ctx_tune)
     int32_t refill_min = 64;
     int32_t blocks_per_cu = 0;   // 0: as many as fit
@@ -375,10 +375,8 @@ extern "C" hz_status hz_ctx_create(int device, uint64_t hbm_budget_bytes, hz_ctx
     const uint64_t gib = 1ull << 30;
     c->budget = hbm_budget_bytes ? hbm_budget_bytes : (free_b > gib ? free_b - gib : free_b / 2);
     for (int d = 0; d < 3; ++d) {
-        c->march_bpc[d] = march_blocks_per_cu(d, 0);
-        c->march_bpc_scene[0][d] = march_blocks_per_cu(d, 1);
-        c->march_bpc_scene[1][d] = march_blocks_per_cu(d, 2);
-        c->march_bpc_scene[2][d] = march_blocks_per_cu(d, 3);
+        for (int k = 0; k < 4; ++k)
+            for (int large = 0; large < 2; ++large) c->march_bpc[large][k][d] = march_blocks_per_cu(d, k, large != 0);
     }
     c->pinned.resize(8);
     // the completion-mark events exist from the start, so issuing a mark
@@ -1359,10 +1357,8 @@ static hz_status prepare_trace(hz_ctx *c, const hz_field *fc, const hz_view *vie
 static int march_grid_blocks(const hz_ctx *c, const TraceLaunch &L, int dt)
 {
     const int64_t want_blocks = march_useful_blocks(L.nslots);
-    const int fit = L.mesh.ntris > 0 ? c->march_bpc_scene[2][dt]
-                    : L.ninner > 0   ? c->march_bpc_scene[1][dt]
-                    : L.nquads > 0   ? c->march_bpc_scene[0][dt]
-                                     : c->march_bpc[dt];
+    const int mode = L.mesh.ntris > 0 ? 3 : L.ninner > 0 ? 2 : L.nquads > 0 ? 1 : 0;
+    const int fit = c->march_bpc[march_large(L.nslots)][mode][dt];
     const int bpc = c->blocks_per_cu > 0 ? std::min(c->blocks_per_cu, fit) : fit;
     return (int)std::max<int64_t>(1, std::min<int64_t>(want_blocks, (int64_t)bpc * c->num_cus));
 }
@@ -1574,9 +1570,9 @@ hz_status ctx_mark(hz_ctx *c, hipStream_t s, CallMark *out) { return mark_issue(
 hz_status ctx_mark_sync(hz_ctx *c, const CallMark &t) { return mark_sync(c, t); }
 void field_use(hz_field *f, const CallMark &t) { field_mark_used(f, t); }
 hz_status field_ready(hz_field *f, hipStream_t s) { return field_order_read(f->ctx, f, s); }
-int march_blocks(hz_ctx *c, int dt, int scene_mode)
+int march_blocks(hz_ctx *c, int dt, int scene_mode, int64_t nslots)
 {
-    return (scene_mode == 0 ? c->march_bpc[dt] : c->march_bpc_scene[scene_mode - 1][dt]) * c->num_cus;
+    return c->march_bpc[march_large(nslots)][scene_mode][dt] * c->num_cus;
 }
 hz_status build_scene(const hz_scene *scene, const hz_grid &g, TraceLaunch *L, std::vector<SceneQuad> &qs,
                       const char *fn)

@@ -272,7 +272,7 @@ static hz_status launch_batch(Server *S, Slot &sl, std::vector<Request *> &batch
     L.refill_min = 64;
     const int dt = (int)field_dtype(head->field);
     const int mode = L.mesh.ntris > 0 ? 3 : L.ninner > 0 ? 2 : L.nquads > 0 ? 1 : 0;
-    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(march_useful_blocks(slot), march_blocks(S->ctx, dt, mode)));
+    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(march_useful_blocks(slot), march_blocks(S->ctx, dt, mode, slot)));
     const bool clear = !sl.counters_clean;
     sl.counters_clean = false;
     // the dispatch packets of the first and last kernel record the batch's

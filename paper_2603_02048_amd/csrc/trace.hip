@@ -621,15 +621,14 @@ __device__ __forceinline__ void wsum(float4 &v, float wgt, const float4 &c)
     v.w = fmaf(wgt, c.w, v.w);
 }
 
-// Grid constants of the march, those of 16-bit float fields in vector registers:
-// an FMA, add or multiply with a scalar-register operand takes the slower of the
-// two issue paths (4.4 against 2.5 cycles of a SIMD measured), and two scalar
-// operands cost a move.  All of them where there is room, with the rows' bases in
-// scalar registers (see FieldRows) or a register budget of five waves (boards,
-// 2 x 960x540: 89.7 us with none, 87.5); with an address per view and row the
-// offsets only (nine requests over four 256^3 F16 fields 3,993 us with none, 3,907
-// with the offsets; with all 3,900, but 21 registers spilled, and chosen rays of
-// such a launch, 700,000 of two views, 1,806 us against 1,657); none with a mesh.
+// Grid constants of the march, those of 16-bit float fields in vector registers
+// where there is room: an FMA, add or multiply with a scalar-register operand
+// takes the slower of the two issue paths (4.4 against 2.5 cycles of a SIMD
+// measured), and two scalar operands cost a move.  All of them where boards leave
+// five waves to a SIMD (2 x 960x540: 89.7 us with none, 87.5); else the offsets of
+// the cell only, which save that move (nine requests over four 256^3 F16 fields
+// 3,993 us with none, 3,907 with the offsets), since with all of them, the same
+// within 0.5%, kernels spill, and fewer waves fit; none with a mesh.
 struct MarchConst {
     float inv_sp[3], off[3];
     float magic;       // 2^23
@@ -920,9 +919,9 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
 {
     const TraceGrid &G = L.grid;
     const TraceStep &S = L.step;
-    const MarchConst K = march_const<DT == DT_F16 && (ONE || SCENE == 2), DT == DT_F16 && SCENE != 3>(G, S);
+    const MarchConst K = march_const<DT == DT_F16 && SCENE == 2, DT == DT_F16 && SCENE != 3>(G, S);
     const FieldRows rows = ONE ? field_rows<DT>(G, L.field) : FieldRows{};
-    constexpr bool LEAN = STEP != kStepPlain;
+    constexpr bool LEAN = STEP != kStepPlain || (SCENE < 2 && DT != DT_F32);
     // LEAN: a step asks once per wave whether any ray is near a face and once per
     // ray whether anything ends it, and sorts these out only then.
     uint32_t nh = 0;
@@ -1227,14 +1226,18 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
     }
 }
 
-// Without boards, or with boards only outside the volume, the march fits six
-// waves per SIMD (at most 80 VGPRs) with no spills; the board-crossing
-// variant fits five (capped at six, it would spill).
-#ifndef HZ_MARCH_F32_WAVES
-#define HZ_MARCH_F32_WAVES 6
-#endif
+// Waves per SIMD: six (at most 80 registers a lane, where some kernels spill up to
+// 18), five with boards or a mesh in the volume.  Seven (72 registers) for F16 up
+// to kLeanSlots, without scene: the chip then holds 458,752 rays at once and not
+// 393,216.  900x506 with 413,000 rays entering 181 us with six, 160 with seven;
+// 1280x720 with 330,000 117 and 120.  Large launches run several rounds either way,
+// and within 72 registers a step takes 1.5% more instructions: 4 x 1920x1080 of
+// 256^3 3,288 us and 3,397.
+template <int DT, int SCENE, int STEP>
+constexpr int march_waves = DT == DT_F16 && SCENE == 0 && STEP == kStepLean ? 7 : 6;
+
 template <int DT, int SCENE, bool ONE, int STEP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DT == DT_F32 ? HZ_MARCH_F32_WAVES : 6)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_waves<DT, SCENE, STEP>)))
 void k_march(TraceLaunch L)
 {
     march<DT, SCENE, ONE, STEP>(L);
@@ -1278,7 +1281,7 @@ static constexpr auto march_kernel()
     else if constexpr (SCENE == 3)
         return &k_march_mesh<DT>;
     else
-        return &k_march<DT, SCENE, ONE, DT != DT_F32 && STEP == kStepPlain ? kStepLean : STEP>;
+        return &k_march<DT, SCENE, ONE, DT == DT_BF16 && STEP == kStepPlain ? kStepLean : STEP>;
 }
 
 // ---------------------------------------------------------------------------
@@ -1388,23 +1391,31 @@ hipError_t launch_march(int dtype, const TraceLaunch &L, int march_blocks, hipSt
     return hipGetLastError();
 }
 
-template <int SCENE>
-static hipError_t occupancy(int dtype, int *nb)
+template <int DT, int SCENE>
+static hipError_t occupancy(bool large, int *nb)
 {
-    if (dtype == DT_F32)
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, march_kernel<DT_F32, SCENE, true, kStepPlain>(), 256, 0);
-    if (dtype == DT_F16)
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, march_kernel<DT_F16, SCENE, true, kStepPlain>(), 256, 0);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, march_kernel<DT_BF16, SCENE, true, kStepPlain>(), 256, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        nb, large ? march_kernel<DT, SCENE, true, kStepPlain>() : march_kernel<DT, SCENE, true, kStepLean>(), 256, 0);
 }
 
-int march_blocks_per_cu(int dtype, int scene_mode)
+template <int SCENE>
+static hipError_t occupancy(int dtype, bool large, int *nb)
+{
+    return dtype == DT_F32   ? occupancy<DT_F32, SCENE>(large, nb)
+           : dtype == DT_F16 ? occupancy<DT_F16, SCENE>(large, nb)
+                             : occupancy<DT_BF16, SCENE>(large, nb);
+}
+
+// Whether a march of that many slots takes the kernels of large launches.
+bool march_large(int64_t nslots) { return nslots > kLeanSlots; }
+
+int march_blocks_per_cu(int dtype, int scene_mode, bool large)
 {
     int nb = 0;
-    const hipError_t e = scene_mode == 3   ? occupancy<3>(dtype, &nb)
-                         : scene_mode == 2 ? occupancy<2>(dtype, &nb)
-                         : scene_mode == 1 ? occupancy<1>(dtype, &nb)
-                                           : occupancy<0>(dtype, &nb);
+    const hipError_t e = scene_mode == 3   ? occupancy<3>(dtype, large, &nb)
+                         : scene_mode == 2 ? occupancy<2>(dtype, large, &nb)
+                         : scene_mode == 1 ? occupancy<1>(dtype, large, &nb)
+                                           : occupancy<0>(dtype, large, &nb);
     if (e != hipSuccess || nb < 1) nb = 1;
     return nb;
 }
