@@ -178,8 +178,12 @@ def _check(status: int, what: str) -> int:
 def _stream(stream) -> C.c_void_p:
     if stream is None:
         # the current stream's handle without a Stream object around it, which
-        # took 3 of the 20 us a small call costs the host
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        # took 3 of the 20 us a small call costs the host; the function is not
+        # part of torch's public interface and may be missing
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return C.c_void_p(raw(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
 

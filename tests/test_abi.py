@@ -60,3 +60,15 @@ def test_null_arguments_are_rejected(haze):
     assert L.hz_field_release(None, None) == haze.E_INVALID
     assert L.hz_ctx_memory(None, None, None) == haze.E_INVALID
     L.hz_ctx_destroy(None)   # ignored
+
+
+def test_current_stream_without_torchs_private_function(haze, monkeypatch):
+    """The handle of the current stream comes from the public Stream object where
+    torch lacks the function that returns it alone."""
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=0x5a0))
+    assert haze._stream(None).value == 0x5a0
