@@ -266,6 +266,39 @@ def test_splat_brick_order_keeps_the_field(ctx, haze):
         ctx.tune("splat.order", 1)
 
 
+@pytest.mark.parametrize("brick_z", [4, 8])
+def test_column_gather_brick_order_keeps_the_field(haze, brick_z):
+    """test_splat_brick_order_keeps_the_field for the gather that orders bricks:
+    a context's first gather, ordered ones, and ones after the grid or the depth
+    changed (the counts of other bricks are not used)."""
+    wls = [W.make_config(1), W.make_small(seed=8, n=6000, res=(40, 24, 16))]
+    parts = [haze.upload_particles(w.particles) for w in wls]
+
+    def field(c, k):
+        f = c.splat_index_field(parts[k], wls[k].grid, wls[k].k_gd, wls[k].h)
+        out = _field_np(c, f)
+        f.release()
+        return out
+
+    def context(order):
+        c = haze.Context(0)
+        c.tune("splat.order", order)
+        c.tune("splat.brick_z", brick_z)
+        return c
+
+    print(f"case column gather order, brick_z={brick_z}", flush=True)
+    with context(0) as plain, context(1) as ordered:
+        ref = [field(plain, 0), field(plain, 1)]
+        runs = [(k, field(ordered, k)) for k in (0, 0, 1, 1, 0, 0)]
+        ordered.tune("splat.brick_z", 12 - brick_z)
+        field(ordered, 0)
+        ordered.tune("splat.brick_z", brick_z)
+        runs += [(0, field(ordered, 0))]
+    for i, (k, got) in enumerate(runs):
+        for x, y in zip(ref[k], got):
+            assert np.array_equal(x.view(np.uint32), y.view(np.uint32)), (i, k)
+
+
 @pytest.mark.parametrize("method", ["gather", "gather8", "scatter"])
 def test_splat_skips_nonfinite_masses(ctx, haze, method):
     """Particles whose mass is NaN or infinite add nothing: the field with a
@@ -314,6 +347,33 @@ def test_splat_methods_on_config2(ctx, haze):
         assert_field_match(dn, (gx, gy, gz), ref[0], ref[1:], wl.grid.spacing, f"config2 splat {method}")
         f.release()
     _default(ctx)
+
+
+# The tests above and below that name the "gather" force a depth, and with it the
+# column gather; these run them with the tile gather, the usual default.
+@pytest.fixture
+def tiles(monkeypatch):
+    monkeypatch.setitem(SPLAT_METHODS, "gather", (1, 0))
+    return "gather"
+
+
+@pytest.mark.parametrize("seed,res,h", [(0, (21, 17, 13), 0.03), (1, (8, 9, 30), 0.05), (2, (2, 3, 2), 0.2),
+                                        (3, (40, 33, 19), 0.02), (4, (24, 20, 10), 0.012), (5, (40, 40, 6), 0.03)])
+def test_tile_gather_parity_small(ctx, haze, tiles, seed, res, h):
+    test_splat_parity_small(ctx, haze, seed, res, h, tiles)
+
+
+def test_tile_gather_skips_nonfinite_masses(ctx, haze, tiles):
+    test_splat_skips_nonfinite_masses(ctx, haze, tiles)
+
+
+def test_tile_gather_on_config2(ctx, haze, tiles, monkeypatch):
+    monkeypatch.delitem(SPLAT_METHODS, "gather8")
+    test_splat_methods_on_config2(ctx, haze)
+
+
+def test_tile_gather_between_scans_and_scatters(ctx, haze, tiles):
+    test_splat_cell_scan_paths(ctx, haze)
 
 
 def test_splat_particles_outside_grid(ctx, haze):
@@ -662,6 +722,44 @@ def test_one_field_march_equals_a_mixed_batch(haze, dtype, res):
             for name, ref in solo[k].items():
                 assert np.array_equal(got[name].view(np.uint8), ref.view(np.uint8)), (t, name)
             ctx.request_release(t)
+        ctx.server_stop()
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("count,least,most", [(4, 1 << 17, 1 << 20), (9, 1 << 20, 1 << 23)])
+def test_one_field_march_equals_a_large_mixed_batch(haze, dtype, count, least, most):
+    """The same past 2^17 slots and past 2^20, where the march takes other
+    kernels: requests over two fields, batched behind one that holds the only
+    slot, give the bits of solo launches."""
+    print(f"case {dtype} {count} requests", flush=True)
+    ctx = haze.Context(0)
+    try:
+        grid = W.make_grid((0.0, 0.0, 0.0), (0.9, 0.8, 1.1), (24, 20, 28))
+        rng = np.random.default_rng(7)
+        fields = [ctx.index_field_from_grid(torch.from_numpy((1e-3 * rng.standard_normal((28, 20, 24))).astype(
+            np.float32)).cuda(), grid, dtype=dtype, store_scale=1.0 if dtype == "f32" else 64.0) for _ in range(2)]
+        step, hold = W.make_steps(grid)
+        hold.ds_uniform *= 0.05
+        views = [W.ring_view(grid.lo, grid.hi, 0.4 + k, 1.1, 401 + 40 * k, 277, backdrop_beyond=0.6) for k in range(2)]
+        each = sum((v.width + 7) // 8 * ((v.height + 7) // 8) * 64 for v in views)
+        assert least < (count - 1) * each and count * each <= most
+        solo = [to_np(ctx.trace_views(f, views, step)) for f in fields]
+        torch.cuda.synchronize()
+        ctx.server_start(slots=1, max_batch_rays=most)
+        first = ctx.submit(fields[0], [W.ring_view(grid.lo, grid.hi, 0.1, 1.0, 1280, 720)], hold)
+        tickets = [ctx.submit(fields[i & 1], views, step) for i in range(count)]
+        _wait_all(ctx, [first] + tickets)
+        launch = [ctx.request_timing(t) for t in tickets]
+        assert max(launch.count(x) for x in launch) >= count - 1   # one launch held them (but perhaps one)
+        for i, t in enumerate(tickets):
+            got = to_np(ctx.request_outputs(t))
+            torch.cuda.synchronize()
+            for name, ref in solo[i & 1].items():
+                assert np.array_equal(got[name].view(np.uint8), ref.view(np.uint8)), (i, name)
+            ctx.request_release(t)
+        ctx.request_release(first)
         ctx.server_stop()
     finally:
         ctx.close()
