@@ -229,16 +229,16 @@ constexpr size_t kCounterSetWords = (size_t)(kMarchHead + 1) * kCounterStride;
 constexpr size_t kCounterBytes = 2 * kCounterSetWords * 4;
 __host__ __device__ inline uint32_t *hit_counter(uint32_t *counters, int k) { return counters + k * kCounterStride; }
 
-// The march deals its rays in batches of 64, one per wave, as long as that
-// gives kMarchSpread waves work; with fewer rays in halved batches (down to
-// kMarchMinBatch rays), and where these are no more than the workgroups, one
-// to a workgroup.  1,024 is one wave per SIMD: below that the launch lasts as
-// long as one wave's steps, and a step is shorter with fewer lanes to gather
-// for and a compute unit to itself; above it, more waves with idle lanes only
-// add issue.  Measured: 4,096 chosen rays of two 1280x720 views 260 us with
-// batches of 64 and four waves to a compute unit, 148 with one, 121 with
-// batches of 16, 116 with batches of 4 (and of 1); halving the batches of two
-// 960x540 views with boards, 2,300 waves, lost 20%.
+// The march deals its rays in batches of 64, one per wave; halved, down to
+// kMarchMinBatch rays, as long as the halved batches number at most kMarchSpread
+// (so 64 from 32,769 rays on); and where there are no more batches than
+// workgroups, one to a workgroup.  1,024 is one wave per SIMD: below that the
+// launch lasts as long as one wave's steps, and a step is shorter with fewer
+// lanes to gather for and a compute unit to itself; above it, more waves with
+// idle lanes only add issue.  Measured: 4,096 chosen rays of two 1280x720 views
+// 260 us with batches of 64 and four waves to a compute unit, 148 with one, 121
+// with batches of 16, 116 with batches of 4 (and of 1); halving the batches of
+// two 960x540 views with boards, 2,300 waves, lost 20%.
 constexpr uint32_t kMarchMinBatch = 4;
 constexpr uint32_t kMarchSpread = 1024;
 __host__ __device__ inline uint32_t march_batch(uint32_t nrays)

@@ -713,8 +713,8 @@ __device__ __forceinline__ void load_pair_at(gpair_ptr p, float4 &a, float4 &b)
 // (x, x + 1 at y; x, x + 1 at y + 1), which wave-uniform registers hold, each
 // less kFieldBias, so that a cell needs one 32-bit offset and no address per
 // row: 12 fewer instructions of a step's about 150.  4 x 1920x1080 of 256^3 F16,
-// bound by issue, 3,520 -> 3,320 us; 8 x 1280x720 of 192^3 F32, bound by its
-// gathers, 1,055 -> 1,041.  Batches that mix fields, and fields past
+// bound by issue, 3,520 -> 3,320 us; 8 x 1280x720 of 128^3 F32, bound by its
+// gathers, 1,057 -> 1,039.  Batches that mix fields, and fields past
 // one_field(), keep an address per view and row; so do scenes in the volume.
 struct FieldRows {
     uint64_t row[4];
@@ -867,9 +867,9 @@ enum { kStepPlain = 0, kStepLean = 1, kStepWalk = 2 };
 // itself cannot: its loads return in order.)  The walk only reads, inside the
 // field, and ends with the rays' chords or with the march, whichever is first.
 // It naps for about 0.4 us per step of the march, so as not to push out of the
-// L2 what it fetched: 4,096 chosen rays of 192^3 113 us without the walk, 112
-// without naps, 99 with 0.2 us, 94 with these, 95 with 0.5; 64x36 rays 154 ->
-// 123, 320x180 170 -> 160, of 64^3 55 -> 51.
+// L2 what it fetched: 4,096 chosen rays of 128^3 113 us without the walk, 112
+// without naps, 99 with 0.2 us, 94 to 98 with these, 95 with 0.5; 64x36 rays 85 ->
+// 78, 320x180 113 -> 105, 128x128 of 64^3 61 -> 55.
 template <int DT, bool ONE>
 __device__ __forceinline__ void walk_ahead(const TraceLaunch &L, uint32_t first, uint32_t sb, uint32_t nh,
                                            const uint32_t *over)
@@ -948,9 +948,9 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
     uint32_t end = min(next + sb, nh);
     // With less than a second batch for each wave, a batch goes to the wave that
     // has finished its first: reserved while its rays were young, the last
-    // batches began after the longest rays had ended.  One F32 view of 2.07
-    // M rays on 192^3, 1.75 batches a wave, 386 -> 354 us, one of 1.2 M 263 ->
-    // 235; BF16 900 -> 800 and 632 -> 541.  From about two batches a wave on the
+    // batches began after the longest rays had ended.  One F32 view of 1600x900
+    // on 128^3, 1.1 batches a wave, 271 -> 247 us, one of 1920x1080, 1.6 batches,
+    // 365 -> 338; BF16 with fixed steps 639 -> 570 and 898 -> 800.  From about two batches a wave on the
     // rounds even out by themselves, and F32 is 2% slower with it.
     const bool late = nh < dyn0 + nwaves * 64u;
     __shared__ uint32_t over;   // the first wave's rays have ended
@@ -1263,14 +1263,14 @@ constexpr bool one_field_march = SCENE < 2;
 
 // The lean step (see march()) is for marches bound by instruction issue or by one
 // ray's steps: of 16-bit fields (4 x 1920x1080 of 256^3 3,320 us against 3,510)
-// and of F32 fields up to 2^20 slots (4,096 chosen rays 112 against 116, 640x360
-// of 128^3 171 against 178, fixed steps 632 against 658).  Larger F32 launches may
+// and of F32 fields up to 2^20 slots (64x36 rays of 128^3 78 against 83, 640x360
+// 114 against 117, 1280x720 the same).  Larger F32 launches may
 // be bound by their gathers (1920x1080 with 1.4 M rays entering 807 against 788,
 // with 0.55 M 336 and 337, 2 x 1280x720 with every ray entering 967 and 950), and
 // with a scene in the volume its tests count most (boards 103 against 99.5).
 constexpr int64_t kLeanSlots = (int64_t)1 << 20;
 // The walk ahead is for launches of at most 32,768 entering rays; larger ones don't
-// carry its code (640x360 of 192^3, 76,800 rays, 171 us without and 175 with it).
+// carry its code (640x360 of 128^3, 71,000 rays, 114 us without and 116 with it).
 constexpr int64_t kWalkSlots = (int64_t)1 << 17;
 
 template <int DT, int SCENE, bool ONE, int STEP>
