@@ -810,7 +810,7 @@ __global__ __launch_bounds__(64 * SPLAT_WAVES) void k_splat(SplatParams P, const
 //      for t and s); the pairs of an inner ring subtract m s^3 / 2 likewise,
 //      from s = 1 - r / h clamped at 0.  (With the mass's cube root, mu, in the
 //      records (mu - mu r / 2h)^3 takes one operation less, 1,735 us against
-//      1,840 at 256^3; but three octaves of masses then share one of roots, and
+//      1,810 at 256^3; but three octaves of masses then share one of roots, and
 //      up to 1.8e-7 of a mass is lost.)
 // What bounds it is VALU issue.  Measured on the card, in cycles of a SIMD per
 // wave64 instruction: FMA, add, multiply 2.5 as long as other waves can issue
@@ -822,7 +822,7 @@ __global__ __launch_bounds__(64 * SPLAT_WAVES) void k_splat(SplatParams P, const
 // matrix cores (v_mfma_f32_16x16x4f32 of (-2v, 1) and (p, |p|^2)) were slower:
 // the FP32 MFMA does not run beside the VALU (8 cycles a slot, against 6 here).
 // Measured, column gather to tiles: 1,048,576 particles on 256^3 voxels 2,060
-// to 1,840 us; 262,144 on 128^3 320 to 255; 16,384 on 64^3 36 to 19; 3,000 on
+// to 1,810 us; 262,144 on 128^3 320 to 250; 16,384 on 64^3 36 to 19; 3,000 on
 // 21x17x13 71 to 11 (here the column gather walks its rows one after another).
 // Every sum runs in a fixed order (ring order within a lane, then the sixteen
 // lanes, then the waves that share an octant), so the field is bitwise
@@ -977,14 +977,14 @@ void k_splat_tiles(SplatParams P, const uint32_t *__restrict__ start, const floa
     const bool second = o0[2] + 2 < P.res[2];   // the second block has voxels
     TileVoxels vox[2];
 #pragma unroll
-    for (int zb = 0; zb < 2; ++zb) {
+    for (int k = 0; k < 4; ++k) vox[0].x[k] = vox[1].x[k] = in_vgpr(fmaf((float)k - 1.5f, T.u[0], -e[0]));
 #pragma unroll
-        for (int k = 0; k < 4; ++k) vox[zb].x[k] = in_vgpr(fmaf((float)k - 1.5f, T.u[0], -e[0]));
+    for (int zb = 0; zb < 2; ++zb) {
         vox[zb].y = fmaf((float)comp - 1.5f, T.u[1], -e[1]);
 #pragma unroll
         for (int g = 0; g < 2; ++g) vox[zb].z[g] = in_vgpr(fmaf((float)(2 * zb + g) - 1.5f, T.u[2], -e[2]));
     }
-    const float ninv = T.ninv;
+    const float ninv = in_vgpr(T.ninv);
     float acc[4][4] = {};
 
     // cell rows that may hold a particle in reach (the slack absorbs rounding:

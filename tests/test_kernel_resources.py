@@ -64,3 +64,10 @@ def test_f16_marches_without_row_bases_do_not_spill(kernels, prefix, count):
     names = [n for n in kernels if n.startswith(prefix)]
     assert len(names) >= count
     assert {n: kernels[n][".vgpr_spill_count"] for n in names} == {n: 0 for n in names}
+
+
+def test_tile_gather_does_not_spill(kernels):
+    """Its particles' loop reloaded three or four registers, as many vector reads again."""
+    names = [n for n in kernels if n.startswith("_ZN4haze13k_splat_tiles")]
+    assert len(names) == 2
+    assert {n: kernels[n][".vgpr_spill_count"] for n in names} == {n: 0 for n in names}
