@@ -1486,7 +1486,7 @@ __global__ __launch_bounds__(256) void k_grad_pack_xyz(const float *__restrict__
 // along the columns through LDS: 256 (F32) or 128 contiguous bytes a read, 128 a
 // write.  One thread per output voxel, reading across z-columns, took 192 us for
 // a 256^3 F32 field; this 106 us (537 MB: 106 us at the rate of a copy).
-// 193x150x111 BF16 46 to 25 us (with the call); in tiles of 32 x 16 (x, z) with
+// 193x150x111 BF16 46 to 22 us; in tiles of 32 x 16 (x, z) with
 // one y a thin field left most lanes idle: 2x4096x4096 F32 1,960 to 221 us (one
 // thread per voxel 476), 4096x4096x2 463 to 190 (277).
 template <int DT, int Z>
