@@ -856,7 +856,9 @@ __device__ __forceinline__ float face_distance(const TraceGrid &G, const float c
                  fminf(c[2] - G.lo[2], G.hi[2] - c[2]));
 }
 
-// How a march steps: plain, lean (see march()), or lean with a second wave walking ahead.
+// How a march steps: plain, lean (see march()), or lean with a second wave walking
+// ahead.  (16-bit fields without a scene in the volume always take the lean step;
+// plain is then the kernel of large launches, where it is another one.)
 enum { kStepPlain = 0, kStepLean = 1, kStepWalk = 2 };
 
 // In launches of few rays the second wave of a workgroup walks straight along
@@ -921,9 +923,9 @@ __device__ __forceinline__ void march(const TraceLaunch &L)
     const TraceStep &S = L.step;
     const MarchConst K = march_const<DT == DT_F16 && SCENE == 2, DT == DT_F16 && SCENE != 3>(G, S);
     const FieldRows rows = ONE ? field_rows<DT>(G, L.field) : FieldRows{};
-    constexpr bool LEAN = STEP != kStepPlain || (SCENE < 2 && DT != DT_F32);
     // LEAN: a step asks once per wave whether any ray is near a face and once per
     // ray whether anything ends it, and sorts these out only then.
+    constexpr bool LEAN = STEP != kStepPlain || (SCENE < 2 && DT != DT_F32);
     uint32_t nh = 0;
     for (int k = 0; k < kRayBins; ++k) nh += *hit_counter(L.counters, k);
     nh = __builtin_amdgcn_readfirstlane(nh);
@@ -1264,10 +1266,10 @@ constexpr bool one_field_march = SCENE < 2;
 // The lean step (see march()) is for marches bound by instruction issue or by one
 // ray's steps: of 16-bit fields (4 x 1920x1080 of 256^3 3,320 us against 3,510)
 // and of F32 fields up to 2^20 slots (64x36 rays of 128^3 78 against 83, 640x360
-// 114 against 117, 1280x720 the same).  Larger F32 launches may
-// be bound by their gathers (1920x1080 with 1.4 M rays entering 807 against 788,
-// with 0.55 M 336 and 337, 2 x 1280x720 with every ray entering 967 and 950), and
-// with a scene in the volume its tests count most (boards 103 against 99.5).
+// 114 against 117, 1280x720 the same).  Larger F32 launches may be bound by their
+// gathers (1920x1080 with 1.4 M rays entering 807 against 788, with 0.55 M 336 and
+// 337, 2 x 1280x720 with every ray entering 967 and 950), and with a scene in the
+// volume its tests count most (boards 103 against 99.5).
 constexpr int64_t kLeanSlots = (int64_t)1 << 20;
 // The walk ahead is for launches of at most 32,768 entering rays; larger ones don't
 // carry its code (640x360 of 128^3, 71,000 rays, 114 us without and 116 with it).
@@ -1281,7 +1283,11 @@ static constexpr auto march_kernel()
     else if constexpr (SCENE == 3)
         return &k_march_mesh<DT>;
     else
-        return &k_march<DT, SCENE, ONE, DT == DT_BF16 && STEP == kStepPlain ? kStepLean : STEP>;
+        return &k_march<DT, SCENE, ONE,
+                        STEP == kStepPlain && DT != DT_F32 &&
+                                march_waves<DT, SCENE, kStepLean> == march_waves<DT, SCENE, kStepPlain>
+                            ? kStepLean
+                            : STEP>;
 }
 
 // ---------------------------------------------------------------------------
